@@ -626,78 +626,155 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(D == 64 
 }
 
 // ---------------------------------------------------------------------------
-// General kernel: any dtype, head_dim <= 256, any stride. One wave per
-// (query row, head); lanes split head_dim, keys are visited in order with an
-// exact (non-lazy) online softmax in fp32.
+// General kernel: any dtype, head_dim <= 256, any stride.
+//
+// A workgroup takes 16 consecutive query rows of one head; its four waves
+// split the history in blocks of 16 keys and merge their partial softmaxes
+// through LDS. Scores and outputs run on the fp32 matrix instructions (fp32
+// in, fp32 accumulation; bf16 inputs convert exactly): S^T = K Q^T leaves
+// lane (l16, g) with keys 4 g .. + 3 of query row l16, which is the B operand
+// of O^T = V^T P^T as it stands, so the weights never leave the registers.
+// Rows of other requests in the tile (a request's edge, or a caller's map in
+// any order) take a pass of their own over their request's history; a pass
+// hands on only its own rows. Against one wave per query row with a
+// cross-lane sum per key (26 us at 256 rows x 2 heads x 32, history 32, fp32)
+// a tile reads K and V once for 16 rows and reduces across lanes once per 16
+// keys: 5 us.
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(64) void dca_attn_generic(
+constexpr int kGenRows = 16;
+
+// DP: head_dim rounded up to 32, 64, 128 or 256. VEC: every row of q, k, x and
+// w_q is aligned to four elements and head_dim (and d_in) a multiple of four.
+template <typename T, int DP, bool VEC>
+__global__ __launch_bounds__(256) void dca_attn_generic(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const int32_t* __restrict__ cand_off, const int32_t* __restrict__ kv_off,
-    T* __restrict__ out, int R, int Tq, int H, int D, int64_t kv_stride, float scale,
-    const int32_t* __restrict__ ids, const T* __restrict__ res, T* __restrict__ out_sum,
-    const T* __restrict__ wq, int d_in) {
-  const int64_t row = blockIdx.x;
-  const int h = blockIdx.y, lane = threadIdx.x;
-  // The request: from the caller's per-candidate map (clamped into [0, R),
-  // so a malformed map gives wrong rows, never an access outside the
+    T* __restrict__ out, int R, int Tq, int64_t n_rows, int H, int D, int64_t kv_stride,
+    float scale, const int32_t* __restrict__ ids, const T* __restrict__ res,
+    T* __restrict__ out_sum, const T* __restrict__ wq, int d_in) {
+  constexpr int NB = DP / 16;              // 16-dim blocks
+  constexpr int LP = DP + 4;               // LDS row (floats), padded against bank conflicts
+  __shared__ __attribute__((aligned(16))) float po[4][kGenRows][LP];   // O, per wave (also Q)
+  __shared__ float pm[4][kGenRows], pl[4][kGenRows];                   // running max, row sum
+  __shared__ int has_keys[kGenRows];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int h = blockIdx.y;
+  const int64_t row0 = (int64_t)blockIdx.x * kGenRows;
+  const int rows = (int)(n_rows - row0 < kGenRows ? n_rows - row0 : kGenRows);
+  const int64_t row = row0 + min(l16, rows - 1);         // clamped; extra rows never stored
+  // The row's request: from the caller's per-candidate map (clamped into
+  // [0, R), so a malformed map gives wrong rows, never an access outside the
   // offsets), else from the CSR offsets.
-  const int r = ids != nullptr ? (int)min((uint32_t)ids[row / Tq], (uint32_t)(R - 1))
-                               : owner_of(cand_off, R, row / Tq);
-  const int64_t a = kv_off[r];
-  const int L = kv_off[r + 1] - (int)a;
-  const int64_t qo = (row * H + h) * D;
-  float qv[4], o[4];
+  const int rq = ids != nullptr ? (int)min((uint32_t)ids[row / Tq], (uint32_t)(R - 1))
+                                : owner_of(cand_off, R, row / Tq);
+  // Query fragments: dims 16 b + 4 g + i of row l16.
+  f32x4 qf[NB];
+  if (wq == nullptr) {
+    const T* qr = q + (row * H + h) * D;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int d = lane + 64 * e;
-    if (wq == nullptr) {
-      qv[e] = d < D ? load_f32(q + qo + d) : 0.f;
-    } else if (d < D) {
-      // The fused query projection: q = x W_q^T for this head's dims,
-      // rounded to T as a separate projection would store it.
-      const T* xr = q + row * d_in;
-      const T* wr = wq + ((int64_t)h * D + d) * d_in;
-      float acc = 0.f;
-      for (int kk = 0; kk < d_in; ++kk) acc = fmaf(load_f32(xr + kk), load_f32(wr + kk), acc);
-      const T qt = from_f32<T>(acc);
-      qv[e] = load_f32(&qt);
-    } else {
-      qv[e] = 0.f;
+    for (int b = 0; b < NB; ++b) qf[b] = load4_f32<T, VEC>(qr + 16 * b + 4 * g, D - 16 * b - 4 * g);
+  } else {
+    // The fused query projection q = x W_q^T for this head's dims, rounded to
+    // T as a separate projection would store it; the waves share the blocks.
+    const T* xr = q + row * d_in;
+    for (int b = wave; b < NB; b += 4) {
+      const int dim = 16 * b + l16;
+      const T* wr = wq + ((int64_t)h * D + dim) * d_in;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+      for (int kk = 4 * g; kk < (d_in + 15) / 16 * 16; kk += 16) {
+        const f32x4 av = load4_f32<T, VEC>(wr + kk, dim < D ? d_in - kk : 0);
+        const f32x4 bv = load4_f32<T, VEC>(xr + kk, d_in - kk);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[i], acc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i] = (float)from_f32<T>(acc[i]);
+      *reinterpret_cast<f32x4*>(&po[0][l16][16 * b + 4 * g]) = acc;
     }
-    o[e] = 0.f;
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < NB; ++b) qf[b] = *reinterpret_cast<const f32x4*>(&po[0][l16][16 * b + 4 * g]);
+    __syncthreads();
   }
-  float m = -INFINITY, l = 0.f;
-  for (int jj = 0; jj < L; ++jj) {
-    const int64_t ko = (a + jj) * kv_stride + (int64_t)h * D;
-    float s = 0.f;
+  uint32_t todo = (1u << rows) - 1u;       // rows whose request has had no pass yet
+  while (todo != 0) {
+    const int r = __builtin_amdgcn_readlane(rq, __builtin_ctz(todo));
+    const bool mine = rq == r;
+    todo &= ~(uint32_t)(__ballot(mine) & 0xffffu);
+    const int64_t a = kv_off[r];
+    const int L = kv_off[r + 1] - (int)a;
+    float m = -INFINITY, lsum = 0.f;
+    f32x4 o[NB];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int d = lane + 64 * e;
-      if (d < D) s = fmaf(qv[e], load_f32(k + ko + d), s);
+    for (int b = 0; b < NB; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int kb = 16 * wave; kb < L; kb += 64) {
+      const T* kr = k + (a + min(kb + l16, L - 1)) * kv_stride + (int64_t)h * D;
+      f32x4 s4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const f32x4 kf = load4_f32<T, VEC>(kr + 16 * b + 4 * g, D - 16 * b - 4 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s4 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i], qf[b][i], s4, 0, 0, 0);
+      }
+      float mx = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s4[i] = kb + 4 * g + i < L ? s4[i] * scale : -INFINITY;
+        mx = fmaxf(mx, s4[i]);
+      }
+      const float mn = fmaxf(m, max_across_rows(mx));
+      const float ms = mn == -INFINITY ? 0.f : mn;       // no finite score yet: weights 0
+      const float alpha = expf(m - ms);
+      f32x4 p;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[i] = expf(s4[i] - ms);
+      lsum = lsum * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
+      m = mn;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int dim = 16 * b + l16;
+        o[b] *= alpha;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int key = kb + 4 * g + i;
+          const float vf = key < L && dim < D
+                               ? load_f32(v + (a + key) * kv_stride + (int64_t)h * D + dim) : 0.f;
+          o[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf, p[i], o[b], 0, 0, 0);
+        }
+      }
     }
+    lsum = sum_across_rows(lsum);
+    if (mine) {
+      if (g == 0) {
+        pm[wave][l16] = m;
+        pl[wave][l16] = lsum;
+        if (wave == 0) has_keys[l16] = L > 0;
+      }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    s *= scale;
-    const float mn = fmaxf(m, s);
-    const float alpha = expf(m - mn), p = expf(s - mn);
-    l = l * alpha + p;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int d = lane + 64 * e;
-      o[e] = o[e] * alpha + (d < D ? p * load_f32(v + ko + d) : 0.f);
+      for (int b = 0; b < NB; ++b)
+        *reinterpret_cast<f32x4*>(&po[wave][l16][16 * b + 4 * g]) = o[b];
     }
-    m = mn;
   }
-  const float inv = L > 0 ? 1.0f / l : 0.f;
+  __syncthreads();
+  // Merge the four partial softmaxes of each row. An empty history gives zeros.
+  for (int idx = threadIdx.x; idx < rows * D; idx += 256) {
+    const int i = idx / D, d = idx - i * D;
+    const float mx = fmaxf(fmaxf(pm[0][i], pm[1][i]), fmaxf(pm[2][i], pm[3][i]));
+    const float ms = mx == -INFINITY ? 0.f : mx;
+    float l = 0.f, y = 0.f;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int d = lane + 64 * e;
-    if (d < D) {
-      const T y = from_f32<T>(o[e] * inv);
-      out[qo + d] = y;
-      if (res != nullptr) out_sum[qo + d] = from_f32<T>(load_f32(&y) + load_f32(res + qo + d));
+    for (int w = 0; w < 4; ++w) {
+      const float f = expf(pm[w][i] - ms);
+      l += pl[w][i] * f;
+      y += po[w][i][d] * f;
     }
+    const T yt = from_f32<T>(has_keys[i] ? y * (1.0f / l) : 0.f);
+    const int64_t at = ((row0 + i) * H + h) * D + d;
+    out[at] = yt;
+    if (res != nullptr) out_sum[at] = from_f32<T>(load_f32(&yt) + load_f32(res + at));
   }
 }
 
@@ -992,13 +1069,24 @@ hipError_t launch_fast_mapped(const AttentionArgs& a, hipStream_t s) {
 
 template <typename T>
 hipError_t launch_generic(const AttentionArgs& a, hipStream_t s) {
-  if (!grid_fits(a.N * a.q_len, 64) || a.heads > 65535) return hipErrorInvalidConfiguration;
-  return launch_kernel(dca_attn_generic<T>, dim3((uint32_t)(a.N * a.q_len), (uint32_t)a.heads),
-                       dim3(64), s, static_cast<const T*>(a.q), static_cast<const T*>(a.k),
-                       static_cast<const T*>(a.v), a.cand_offsets, a.kv_offsets,
-                       static_cast<T*>(a.out), (int)a.R, a.q_len, a.heads, a.head_dim,
-                       a.kv_stride, a.scale, a.ids, static_cast<const T*>(a.residual),
-                       static_cast<T*>(a.out_sum), static_cast<const T*>(a.proj_w), a.proj_in);
+  const int64_t rows = a.N * a.q_len;
+  const int64_t blocks = (rows + kGenRows - 1) / kGenRows;
+  if (!grid_fits(blocks, 256) || a.heads > 65535) return hipErrorInvalidConfiguration;
+  auto ok = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % (4 * sizeof(T)) == 0; };
+  const bool vec = a.head_dim % 4 == 0 && a.kv_stride % 4 == 0 && ok(a.q) && ok(a.k) &&
+                   (a.proj_w == nullptr || (ok(a.proj_w) && a.proj_in % 4 == 0));
+  auto go = [&](auto kernel) {
+    return launch_kernel(kernel, dim3((uint32_t)blocks, (uint32_t)a.heads), dim3(256), s,
+                         static_cast<const T*>(a.q), static_cast<const T*>(a.k),
+                         static_cast<const T*>(a.v), a.cand_offsets, a.kv_offsets,
+                         static_cast<T*>(a.out), (int)a.R, a.q_len, rows, a.heads, a.head_dim,
+                         a.kv_stride, a.scale, a.ids, static_cast<const T*>(a.residual),
+                         static_cast<T*>(a.out_sum), static_cast<const T*>(a.proj_w), a.proj_in);
+  };
+  if (a.head_dim <= 32) return vec ? go(dca_attn_generic<T, 32, true>) : go(dca_attn_generic<T, 32, false>);
+  if (a.head_dim <= 64) return vec ? go(dca_attn_generic<T, 64, true>) : go(dca_attn_generic<T, 64, false>);
+  if (a.head_dim <= 128) return vec ? go(dca_attn_generic<T, 128, true>) : go(dca_attn_generic<T, 128, false>);
+  return vec ? go(dca_attn_generic<T, 256, true>) : go(dca_attn_generic<T, 256, false>);
 }
 
 }  // namespace

@@ -60,6 +60,28 @@ __device__ __forceinline__ u32x4 load16(const void* p, bool ok) {
   return v;
 }
 
+// Four consecutive elements p[0 .. n) as floats, zeros past n. VEC: one load;
+// n is then at most 0 or at least 4, and p aligned to four elements.
+template <typename T, bool VEC>
+__device__ __forceinline__ f32x4 load4_f32(const T* p, int n) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (VEC) {
+    if (n > 0) {
+      if constexpr (sizeof(T) == 4) {
+        v = *reinterpret_cast<const f32x4*>(p);
+      } else {
+        const u32x2 b = *reinterpret_cast<const u32x2*>(p);
+        v = f32x4{bf16_lo(b[0]), bf16_hi(b[0]), bf16_lo(b[1]), bf16_hi(b[1])};
+      }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i < n) v[i] = load_f32(p + i);
+  }
+  return v;
+}
+
 // Owner of candidate n under CSR offsets: the largest r in [0, R) with
 // off[r] <= n. Empty requests (off[r] == off[r+1]) are skipped naturally.
 __device__ __forceinline__ int owner_of(const int32_t* __restrict__ off, int R, int64_t n) {

@@ -827,45 +827,129 @@ void ikbo_gemm_stream(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w
 
 // ---------------------------------------------------------------------------
 // General path: any dtype, any K / D, no alignment requirements.
+//
+// One TS x TS output tile (features x rows) per workgroup and step; its four
+// waves split K and reduce through LDS in a fixed order. The products run on
+// the fp32 matrix instructions (fp32 in, fp32 accumulation; bf16 inputs
+// convert exactly), operands straight from global memory: lane (row l % TS,
+// group l / TS) loads four consecutive k of its feature row and of its
+// candidate row, and the i-th matrix instruction of a step takes the i-th
+// element of both, so any k order inside a step is the same for both
+// operands. Small calls are bound by latency: the split over waves keeps a
+// wave's chain short and 16 x 16 tiles spread a few hundred rows over all
+// CUs. At 256 rows, 384 -> 256, fp32, this form takes 4 us where one thread
+// per output took 57 us in two launches.
+//
+// EXT (small calls): the request term is taken as k_req further columns of
+// the candidate's own product, w_req and x_req[m_n] read per row, so a call
+// is one launch and no request table is formed.
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void request_gemm_generic(
-    const T* __restrict__ x, const T* __restrict__ w, float* __restrict__ z,
-    const int32_t* __restrict__ off, int32_t* __restrict__ ids, int R, int64_t N, int K, int D,
-    int z_blocks) {
-  if ((int)blockIdx.x >= z_blocks) {
-    const int64_t n = (int64_t)(blockIdx.x - z_blocks) * 256 + threadIdx.x;
-    if (n < N) ids[n] = owner_of(off, R, n);
-    return;
-  }
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (int64_t)R * D) return;
-  const int r = (int)(idx / D), d = (int)(idx % D);
-  float acc = 0.f;
-  for (int k = 0; k < K; ++k)
-    acc = fmaf(load_f32(x + (int64_t)r * K + k), load_f32(w + (int64_t)d * K + k), acc);
-  z[idx] = acc;
-}
+constexpr int64_t kExtMaxWork = int64_t(1) << 27;   // N d_out k_req up to which EXT runs
 
 template <typename T>
-__global__ __launch_bounds__(256) void linear_generic(
-    const T* __restrict__ x, const T* __restrict__ xadd, const T* __restrict__ w,
-    const float* __restrict__ bias, const float* __restrict__ z, const int32_t* __restrict__ ids,
-    T* __restrict__ out, int64_t N, int K, int D, int relu, int R) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= N * D) return;
-  const int64_t n = idx / D;
-  const int d = (int)(idx % D);
-  float acc = 0.f;
-  for (int k = 0; k < K; ++k) {
-    float xv = load_f32(x + n * K + k);
-    if (xadd != nullptr) xv = (float)from_f32<T>(xv + load_f32(xadd + n * K + k));
-    acc = fmaf(xv, load_f32(w + (int64_t)d * K + k), acc);
+struct GeneralArgs {
+  const T* x;              // [N, K]
+  const T* xadd;           // [N, K] or NULL
+  const T* w;              // [D, K]
+  const T* x2;             // EXT: x_req [R, K2]
+  const T* w2;             // EXT: w_req [D, K2]
+  const float* bias;       // [D] or NULL
+  const float* z;          // request table [R, D] or NULL
+  const int32_t* off;      // CSR offsets [R + 1], or
+  const int32_t* ids;      // a request id per row (with z or EXT)
+  void* out;               // [N, D] T, or float when OUTF
+  int64_t N;
+  int K, K2, D, R, relu, tiles_m;
+  int64_t tiles;
+};
+
+template <typename T, int TS, bool VEC, bool OUTF, bool EXT>
+__global__ __launch_bounds__(256) void linear_general(GeneralArgs<T> a) {
+  constexpr int NG = 64 / TS;              // lane groups: k values per matrix instruction
+  constexpr int CH = 4 * NG;               // k per step
+  constexpr int NA = TS * TS / 64;         // accumulators per lane (4 or 16)
+  typedef float acc_t __attribute__((ext_vector_type(NA)));
+  __shared__ f32x4 red[NA / 4][4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l = lane % TS, g = lane / TS;
+  for (int64_t t = blockIdx.x; t < a.tiles; t += gridDim.x) {
+    const int d0 = (int)(t % a.tiles_m) * TS;
+    const int64_t n0 = t / a.tiles_m * TS;
+    const int d = d0 + l;                  // this lane's feature row of W ...
+    const int64_t n = n0 + l;              // ... and its candidate
+    const bool dok = d < a.D, nok = n < a.N;
+    int r = 0;
+    if ((EXT || a.z != nullptr) && nok)
+      r = a.ids != nullptr ? (int)min((uint32_t)a.ids[n], (uint32_t)(a.R - 1))
+                           : owner_of(a.off, a.R, n);
+    acc_t acc;
+#pragma unroll
+    for (int e = 0; e < NA; ++e) acc[e] = 0.f;
+    auto product = [&](const T* xp, const T* xap, const T* wp, int K) __attribute__((always_inline)) {
+#pragma unroll 4
+      for (int k = CH * wave + 4 * g; k < (K + CH - 1) / CH * CH; k += 4 * CH) {
+        const int left = K - k;
+        const f32x4 av = load4_f32<T, VEC>(wp + k, dok ? left : 0);
+        f32x4 bv = load4_f32<T, VEC>(xp + k, nok ? left : 0);
+        if (xap != nullptr) {              // GLM pointwise residual: round(x + x_add)
+          bv += load4_f32<T, VEC>(xap + k, nok ? left : 0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) bv[i] = (float)from_f32<T>(bv[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if constexpr (TS == 16) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[i], acc, 0, 0, 0);
+          else acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[i], acc, 0, 0, 0);
+        }
+      }
+    };
+    product(a.x + n * a.K, a.xadd != nullptr ? a.xadd + n * a.K : nullptr,
+            a.w + (int64_t)d * a.K, a.K);
+    if constexpr (EXT)
+      product(a.x2 + (int64_t)r * a.K2, nullptr, a.w2 + (int64_t)d * a.K2, a.K2);
+    // Quad q of the accumulators: features d0 + 4 NG q + 4 g .. + 3 of candidate n.
+#pragma unroll
+    for (int q = 0; q < NA / 4; ++q)
+      red[q][wave][lane] = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    __syncthreads();
+    for (int q = wave; q < NA / 4; q += 4) {
+      f32x4 s = ((red[q][0][lane] + red[q][1][lane]) + red[q][2][lane]) + red[q][3][lane];
+      const int df = d0 + 4 * NG * q + 4 * g;
+      if (!nok) continue;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (df + i >= a.D) break;
+        if (!EXT && a.z != nullptr) s[i] += a.z[(int64_t)r * a.D + df + i];
+        if (a.bias != nullptr) s[i] += a.bias[df + i];
+        if (a.relu) s[i] = fmaxf(s[i], 0.f);
+        const int64_t o = n * a.D + df + i;
+        if constexpr (OUTF) static_cast<float*>(a.out)[o] = s[i];
+        else static_cast<T*>(a.out)[o] = from_f32<T>(s[i]);
+      }
+    }
+    __syncthreads();                       // red is free for the next tile
   }
-  if (z != nullptr) acc += z[(int64_t)min((uint32_t)ids[n], (uint32_t)(R - 1)) * D + d];
-  if (bias != nullptr) acc += bias[d];
-  if (relu) acc = fmaxf(acc, 0.f);
-  out[idx] = from_f32<T>(acc);
+}
+
+template <typename T, bool OUTF, bool EXT>
+hipError_t launch_general(GeneralArgs<T> g, hipStream_t s) {
+  // 32 x 32 tiles read half the operand bytes per product; 16 x 16 tiles while
+  // the larger ones would leave CUs without a workgroup.
+  const bool small = ((g.N + 31) / 32) * ((g.D + 31) / 32) < 512;
+  const int ts = small ? 16 : 32;
+  g.tiles_m = (g.D + ts - 1) / ts;
+  g.tiles = (g.N + ts - 1) / ts * g.tiles_m;
+  const uint32_t grid = (uint32_t)(g.tiles < (1 << 20) ? g.tiles : (1 << 20));
+  // Four-element loads need every row of every operand aligned to them.
+  auto ok = [](const void* p, int k) {
+    return k % 4 == 0 && reinterpret_cast<uintptr_t>(p) % (4 * sizeof(T)) == 0;
+  };
+  const bool vec = ok(g.x, g.K) && ok(g.xadd, g.K) && ok(g.w, g.K) && ok(g.x2, g.K2) &&
+                   ok(g.w2, g.K2);
+  auto go = [&](auto kernel) { return launch_kernel(kernel, dim3(grid), dim3(256), s, g); };
+  if (small)
+    return vec ? go(linear_general<T, 16, true, OUTF, EXT>) : go(linear_general<T, 16, false, OUTF, EXT>);
+  return vec ? go(linear_general<T, 32, true, OUTF, EXT>) : go(linear_general<T, 32, false, OUTF, EXT>);
 }
 
 template <int BM, int BN, int BK, int WMW, int WNW>
@@ -892,25 +976,39 @@ hipError_t launch_fast_gemm(const LinearArgs& a, hipStream_t s) {
 
 template <typename T>
 hipError_t launch_generic(const LinearArgs& a, hipStream_t s) {
-  hipError_t e = hipSuccess;
-  if (a.k_req > 0) {
-    if (!grid_fits((a.R * a.d_out + 255) / 256 + (a.N + 255) / 256, 256))
-      return hipErrorInvalidConfiguration;
-    const int z_blocks = (int)((a.R * a.d_out + 255) / 256);
-    const int id_blocks = a.ids_given ? 0 : (int)((a.N + 255) / 256);
-    e = launch_kernel(request_gemm_generic<T>, dim3(z_blocks + id_blocks), dim3(256), s,
-                      static_cast<const T*>(a.x_req), static_cast<const T*>(a.w_req), a.z,
-                      a.cand_offsets, a.ids, (int)a.R, a.N, (int)a.k_req, (int)a.d_out,
-                      z_blocks);
-    if (e != hipSuccess) return e;
+  GeneralArgs<T> g{};
+  g.x = static_cast<const T*>(a.x_cand);
+  g.xadd = static_cast<const T*>(a.x_cand_add);
+  g.w = static_cast<const T*>(a.w_cand);
+  g.bias = a.bias;
+  g.out = a.out;
+  g.N = a.N;
+  g.K = (int)a.k_cand;
+  g.D = (int)a.d_out;
+  g.R = (int)a.R;
+  g.relu = (int)a.relu;
+  if (a.k_req == 0) return launch_general<T, false, false>(g, s);
+  g.off = a.cand_offsets;
+  g.ids = a.ids_given ? a.ids : nullptr;
+  // The request term inside the candidate product costs N / R times the
+  // request table's work, the table a launch of its own (5 us and more).
+  if (a.N * a.d_out <= kExtMaxWork / a.k_req) {
+    g.x2 = static_cast<const T*>(a.x_req);
+    g.w2 = static_cast<const T*>(a.w_req);
+    g.K2 = (int)a.k_req;
+    return launch_general<T, false, true>(g, s);
   }
-  const int64_t blocks = (a.N * a.d_out + 255) / 256;
-  if (!grid_fits(blocks, 256)) return hipErrorInvalidConfiguration;
-  return launch_kernel(linear_generic<T>, dim3((uint32_t)blocks), dim3(256), s,
-                       static_cast<const T*>(a.x_cand), static_cast<const T*>(a.x_cand_add),
-                       static_cast<const T*>(a.w_cand), a.bias,
-                       a.k_req > 0 ? a.z : nullptr, a.ids, static_cast<T*>(a.out), a.N,
-                       (int)a.k_cand, (int)a.d_out, (int)a.relu, (int)a.R);
+  GeneralArgs<T> r{};
+  r.x = static_cast<const T*>(a.x_req);
+  r.w = static_cast<const T*>(a.w_req);
+  r.out = a.z;
+  r.N = a.R;
+  r.K = (int)a.k_req;
+  r.D = (int)a.d_out;
+  const hipError_t e = launch_general<T, true, false>(r, s);
+  if (e != hipSuccess) return e;
+  g.z = a.z;
+  return launch_general<T, false, false>(g, s);
 }
 
 }  // namespace
