@@ -793,17 +793,17 @@ __device__ __forceinline__ int clamp_request(int32_t m, int R) {
   return (int)min((uint32_t)m, (uint32_t)(R - 1));
 }
 
-__global__ __launch_bounds__(256) void group_count(const int32_t* __restrict__ ids, int64_t N,
-                                                   int R, int64_t G, int nb,
-                                                   int32_t* __restrict__ hist) {
+__global__ __launch_bounds__(1024) void group_count(const int32_t* __restrict__ ids, int64_t N,
+                                                    int R, int64_t G, int nb,
+                                                    int32_t* __restrict__ hist) {
   __shared__ int cnt[kGroupMaxRequests];
   const int b = blockIdx.x;
-  for (int r = threadIdx.x; r < R; r += 256) cnt[r] = 0;
+  for (int r = threadIdx.x; r < R; r += 1024) cnt[r] = 0;
   __syncthreads();
   const int64_t lo = (int64_t)b * G, hi = min(lo + G, N);
-  for (int64_t i = lo + threadIdx.x; i < hi; i += 256) atomicAdd(&cnt[clamp_request(ids[i], R)], 1);
+  for (int64_t i = lo + threadIdx.x; i < hi; i += 1024) atomicAdd(&cnt[clamp_request(ids[i], R)], 1);
   __syncthreads();
-  for (int r = threadIdx.x; r < R; r += 256) hist[(int64_t)r * nb + b] = cnt[r];
+  for (int r = threadIdx.x; r < R; r += 1024) hist[(int64_t)r * nb + b] = cnt[r];
 }
 
 // One workgroup: exclusive scan of hist[0 .. total) in place (each thread
@@ -838,33 +838,114 @@ __global__ __launch_bounds__(1024) void group_scan(int32_t* __restrict__ hist, i
   if (t == 0) grp_off[R] = (int)N;
 }
 
-// One wave per block, walking its candidates in order 64 at a time: lanes
-// holding the same request take consecutive slots from that request's
-// cursor in lane order (ballot ranks), so the order within a request is
-// the original one.
-__global__ __launch_bounds__(64) void group_scatter(const int32_t* __restrict__ ids, int64_t N,
-                                                    int R, int64_t G, int nb,
-                                                    const int32_t* __restrict__ base,
-                                                    int32_t* __restrict__ order) {
-  __shared__ int cursor[kGroupMaxRequests];
-  const int b = blockIdx.x, lane = threadIdx.x;
-  for (int r = lane; r < R; r += 64) cursor[r] = base[(int64_t)r * nb + b];
+// One workgroup per block, each of its waves owning a contiguous share of the
+// block's candidates: the waves count their shares, a prefix over the waves
+// turns the counts into each wave's cursors, then every wave walks its share
+// in order 64 candidates at a time. Lanes holding the same request are found
+// by one ballot per bit of the request id and take consecutive slots in lane
+// order, so the order within a request is the original one. The time is the
+// length of a wave's serial walk: 16 waves take 13 us for 8192 candidates of
+// 16 requests, counting included, where one wave per 4096 candidates visiting
+// the requests of its 64 lanes one by one took 150 us (and 13 us to count).
+// WHOLE (one block, N up to kGroupWholeCands): the counts are scanned here
+// too and the grouped offsets written, in one launch instead of three.
+constexpr int kGroupCounters = 32768;              // per-wave request counters in LDS (128 KiB)
+constexpr int64_t kGroupWholeCands = 32768;
+constexpr int kGroupAhead = 8;                     // rounds of 64 ids in flight
+
+template <bool WHOLE>
+__global__ __launch_bounds__(1024) void group_scatter(const int32_t* __restrict__ ids, int64_t N,
+                                                      int R, int64_t G, int nb, int key_bits,
+                                                      const int32_t* __restrict__ base,
+                                                      int32_t* __restrict__ grp_off,
+                                                      int32_t* __restrict__ order) {
+  __shared__ int cnt[kGroupCounters];               // [wave][R]
+  __shared__ int part[16];
+  volatile int* const cursors = cnt;                // written by other lanes of the wave
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int NT = blockDim.x, W = NT / 64;
+  for (int i = tid; i < W * R; i += NT) cnt[i] = 0;
   __syncthreads();
   const int64_t lo = (int64_t)b * G, hi = min(lo + G, N);
+  const int64_t share = ((hi - lo + W - 1) / W + 63) / 64 * 64;
+  const int64_t wlo = min(lo + wave * share, hi), whi = min(wlo + share, hi);
+  // Ids are loaded kGroupAhead rounds at a time: one memory latency for all.
+  for (int64_t c = wlo + lane; c < whi; c += 64 * kGroupAhead) {
+    int key[kGroupAhead];
+#pragma unroll
+    for (int j = 0; j < kGroupAhead; ++j)
+      key[j] = c + 64 * j < whi ? clamp_request(ids[c + 64 * j], R) : -1;
+#pragma unroll
+    for (int j = 0; j < kGroupAhead; ++j)
+      if (key[j] >= 0) atomicAdd(&cnt[wave * R + key[j]], 1);
+  }
+  __syncthreads();
+  // Counts -> cursors: the request's first position (its scan over the
+  // requests, or the caller's), then a prefix over the waves.
+  int run = 0;
+  if constexpr (WHOLE) {
+    // Requests in rounds of one per thread, scanned over the workgroup.
+    for (int r0 = 0; r0 < R; r0 += NT) {
+      const int r = r0 + tid;
+      int sum = 0;
+      if (r < R)
+        for (int w = 0; w < W; ++w) sum += cnt[w * R + r];
+      int incl = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
+      }
+      if (lane == 63) part[wave] = incl;
+      __syncthreads();
+      int at = run + incl - sum, total = 0;
+      for (int w = 0; w < W; ++w) {
+        if (w < wave) at += part[w];
+        total += part[w];
+      }
+      run += total;
+      if (r < R) {
+        grp_off[r] = at;
+        for (int w = 0; w < W; ++w) {
+          const int c = cnt[w * R + r];
+          cnt[w * R + r] = at;
+          at += c;
+        }
+      }
+      __syncthreads();                              // part is free for the next round
+    }
+    if (tid == 0) grp_off[R] = (int)N;
+  } else {
+    for (int r = tid; r < R; r += NT) {
+      int at = base[(int64_t)r * nb + b];
+      for (int w = 0; w < W; ++w) {
+        const int c = cnt[w * R + r];
+        cnt[w * R + r] = at;
+        at += c;
+      }
+    }
+    __syncthreads();
+  }
   const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int64_t c = lo; c < hi; c += 64) {
-    const int64_t i = c + lane;
-    const bool valid = i < hi;
-    const int key = valid ? clamp_request(ids[i], R) : -1;
-    uint64_t todo = __ballot(valid);
-    while (todo != 0) {
-      const int leader = __builtin_ctzll(todo);
-      const int k0 = __shfl(key, leader);
-      const uint64_t same = __ballot(valid && key == k0);
-      const int at = cursor[k0];                          // read by every lane first ...
-      if (valid && key == k0) order[at + __builtin_popcountll(same & below)] = (int)i;
-      if (lane == leader) cursor[k0] = at + __builtin_popcountll(same);   // ... then advanced
-      todo &= ~same;
+  for (int64_t c = wlo; c < whi; c += 64 * kGroupAhead) {
+    int keys[kGroupAhead];
+#pragma unroll
+    for (int j = 0; j < kGroupAhead; ++j)
+      keys[j] = c + 64 * j + lane < whi ? clamp_request(ids[c + 64 * j + lane], R) : -1;
+#pragma unroll
+    for (int j = 0; j < kGroupAhead; ++j) {
+      const int key = keys[j];
+      uint64_t same = __ballot(key >= 0);
+      for (int bit = 0; bit < key_bits; ++bit) {
+        const uint64_t m = __ballot((key >> bit) & 1);
+        same &= (key >> bit) & 1 ? m : ~m;
+      }
+      if (key >= 0) {
+        const int at = cursors[wave * R + key];     // read by every lane first ...
+        order[at + __builtin_popcountll(same & below)] = (int)(c + 64 * j + lane);
+        if ((same & below) == 0)                    // ... then advanced by the group's first
+          cursors[wave * R + key] = at + __builtin_popcountll(same);
+      }
     }
   }
 }
@@ -1055,14 +1136,26 @@ hipError_t launch_fast_mapped(const AttentionArgs& a, hipStream_t s) {
   int32_t* order = reinterpret_cast<int32_t*>(ws + align_up256((size_t)(a.R + 1) * 4));
   int32_t* hist = reinterpret_cast<int32_t*>(ws + align_up256((size_t)(a.R + 1) * 4) +
                                              align_up256((size_t)a.N * 4));
-  hipError_t e = launch_kernel(group_count, dim3((uint32_t)nb), dim3(256), s, a.ids, a.N,
-                               (int)a.R, G, nb, hist);
-  if (e == hipSuccess)
-    e = launch_kernel(group_scan, dim3(1), dim3(1024), s, hist, a.R * (int64_t)nb, (int)a.R, nb,
-                      a.N, grp_off);
-  if (e == hipSuccess)
-    e = launch_kernel(group_scatter, dim3((uint32_t)nb), dim3(64), s, a.ids, a.N, (int)a.R, G,
-                      nb, static_cast<const int32_t*>(hist), order);
+  int waves = 16, key_bits = 0;
+  while (waves > 1 && waves * a.R > kGroupCounters) waves /= 2;
+  while ((int64_t(1) << key_bits) < a.R) ++key_bits;
+  const int32_t* base = hist;
+  hipError_t e;
+  // One launch while a wave's walk (N / 16 candidates) stays within a few
+  // microseconds and every request has its counters in all 16 waves.
+  if (a.N <= kGroupWholeCands && waves == 16) {
+    e = launch_kernel(group_scatter<true>, dim3(1), dim3(1024), s, a.ids, a.N, (int)a.R, a.N, 1,
+                      key_bits, base, grp_off, order);
+  } else {
+    e = launch_kernel(group_count, dim3((uint32_t)nb), dim3(1024), s, a.ids, a.N, (int)a.R, G, nb,
+                      hist);
+    if (e == hipSuccess)
+      e = launch_kernel(group_scan, dim3(1), dim3(1024), s, hist, a.R * (int64_t)nb, (int)a.R, nb,
+                        a.N, grp_off);
+    if (e == hipSuccess)
+      e = launch_kernel(group_scatter<false>, dim3((uint32_t)nb), dim3(64 * waves), s, a.ids, a.N,
+                        (int)a.R, G, nb, key_bits, base, grp_off, order);
+  }
   if (e != hipSuccess) return e;
   return launch_fast<D, true>(a, grp_off, order, s);
 }

@@ -406,3 +406,26 @@ def test_attention_proj_with_plan(gpu_lib):
     torch.cuda.synchronize()
     assert torch.equal(out, ref_out) and torch.equal(out_sum, ref_sum)
     assert_close(host(out), want, "proj planned")
+
+
+# The grouping's edges: one workgroup up to 32768 candidates with counters in
+# all 16 waves (R <= 2048), then blocks with 16, 8 and 2 waves; the last
+# partial 64 of a wave's share; ids outside [0, R) clamped.
+@pytest.mark.parametrize("n,r", [(1, 1), (65, 2), (1025, 1), (3000, 2048), (3000, 2049),
+                                 (32768, 41), (32769, 41), (20000, 16384)])
+def test_mapped_grouping_edges(gpu_lib, n, r):
+    rng = np.random.default_rng(n + r)
+    m = rng.integers(0, r, n).astype(np.int32)
+    m[rng.integers(0, n)] = r + 5
+    q = torch.zeros((n, 1, 1, 64), dtype=torch.bfloat16, device="cuda")
+    v = torch.arange(r, device="cuda").to(torch.bfloat16).view(r, 1, 1).expand(r, 1, 64).contiguous()
+    ws = torch.zeros(ops.dca_attention_mapped_workspace_size(r, n), dtype=torch.uint8,
+                     device="cuda")
+    got = host(ops.dca_attention_mapped(q, torch.zeros_like(v), v, dev_i32(m),
+                                        dev_i32(np.arange(r + 1)), workspace=ws))
+    m = np.minimum(m, r - 1)
+    raw = ws.cpu().numpy().view(np.int32)
+    order = raw[256 // 4 * (((r + 1) * 4 + 255) // 256):][:n]
+    np.testing.assert_array_equal(order, np.argsort(m, kind="stable"))
+    np.testing.assert_array_equal(raw[:r + 1], np.concatenate([[0], np.cumsum(np.bincount(m, minlength=r))]))
+    np.testing.assert_array_equal(got[:, 0, 0, 0], host(v)[m, 0, 0])
