@@ -36,8 +36,9 @@ __global__ __launch_bounds__(256) void glm_fm_bf16(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, g = lane >> 4;
   const uint32_t slot = xcd_remap(blockIdx.x, gridDim.x);
-  const int r = request_of_slot(off, R, slot, FC, kFmRows);
-  const int64_t j = (int64_t)slot - tile_base(off, r, FC, kFmRows);
+  // Without the candidate side there is one slot per request.
+  const int r = yc == nullptr ? (int)slot : request_of_slot(off, R, slot, FC, kFmRows);
+  const int64_t j = yc == nullptr ? 0 : (int64_t)slot - tile_base(off, r, FC, kFmRows);
   const int64_t rbeg = (int64_t)off[r] * FC, rend = (int64_t)off[r + 1] * FC;
   const bf16_t* xrr = xr + (int64_t)r * FR * E;
   const int KS = E / 32, JB = FR / 16;
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(256) void glm_fm_cand_generic(const T* __restrict__
 
 template <int FC>
 hipError_t launch_fast(const InteractionArgs& a, hipStream_t s) {
-  const int64_t slots = a.R + (a.N * FC + kFmRows - 1) / kFmRows;
+  const int64_t slots = a.R + (a.y_cand != nullptr ? (a.N * FC + kFmRows - 1) / kFmRows : 0);
   if (!grid_fits(slots, 256)) return hipErrorInvalidConfiguration;
   return launch_kernel(glm_fm_bf16<FC>, dim3((uint32_t)slots), dim3(256), s,
                        static_cast<const bf16_t*>(a.x_req), static_cast<const bf16_t*>(a.x_cand),

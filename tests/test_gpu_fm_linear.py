@@ -130,3 +130,17 @@ def test_workload4_shape_sampled(gpu_lib):
     want = pipelines.fm_linear(w, rows=rows)
     assert_close(got[rows], want["out"], "workload 4")
     assert_close(y_req, want["y_req"], "workload 4 Y^R")
+
+
+# The block walk and the feature slices: runs of one, two and several blocks
+# per workgroup, blocks of one candidate, waves without features (320 of 512),
+# slices of 64 (d 576), 512 (1024) and the largest d_out.
+@pytest.mark.parametrize("counts,d", [([1, 31, 32, 33, 0, 64], 320), ([9000, 1, 0, 7003], 192),
+                                      ([3] * 300, 576), ([8300, 9100, 17], 1024), ([40, 7], 4096)],
+                         ids=lambda v: f"N{sum(v)}" if isinstance(v, list) else f"d{v}")
+def test_fused_block_walk_and_slices(gpu_lib, counts, d):
+    c = wl.fm_linear_case(counts, 32, 8, 128, d, seed=d)
+    got, _ = _run(c)
+    n = c.n_cand
+    rows = np.unique(np.concatenate([np.arange(0, n, max(1, n // 400)), c.cand_offsets[1:] - 1]))
+    assert_close(got[rows], _want(c, rows=rows)[0], f"fm_linear N{n} d{d}")
