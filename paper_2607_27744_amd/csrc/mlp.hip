@@ -8,43 +8,46 @@
 // Run as two launches of the linear kernel, H makes a round trip through HBM
 // (written once, read once: 2 d_hidden bytes per candidate each way, four
 // times the 2 k_cand + 2 d_out bytes the pair needs at the retrieval shape).
-// Here a persistent workgroup (one per CU) walks 128-candidate tiles (four
-// waves of 32, one wave per SIMD). A wave keeps its candidates' X^C rows in
-// registers and walks the hidden layer in chunks of 64 units: the chunk's 64
-// rows of W1_CC and 64 columns of W2 come through a two-slot LDS ring (DMA
-// loads, one chunk ahead, as one stream across tiles since every tile needs
-// the same weights); the wave computes its 64 x 32 block of H^T on the matrix
-// cores, adds the Zb row of each candidate's request and the activation,
-// rounds to bf16, and feeds it straight back as the operand of the second
-// product. H never leaves the registers. During a tile's last chunk the next
-// tile's X^C rows and Zb rows are loaded, so a tile starts without a wait.
+// Here a persistent workgroup (one per CU, eight waves, two per SIMD) walks
+// 128-candidate tiles with the tile's X^C rows in registers and the hidden
+// layer in chunks of 64 units: the chunk's 64 rows of W1_CC and 64 columns of
+// W2 come through a two-slot LDS ring (DMA loads, one chunk ahead, as one
+// stream across tiles since every tile needs the same weights). Per chunk
+//   1. the waves, as 2 hidden blocks x 4 candidate blocks of 32, compute H^T
+//      on the matrix cores on top of the Zb values of each lane's own request,
+//      apply the activation and write bf16 H to LDS;
+//   2. the waves, as 4 output quarters x 2 candidate halves of 64, add
+//      W2 H to their accumulators.
+// Chunk c's step 1 and chunk c - 1's step 2 share one barrier interval.
+// What bounds it: LDS, which per chunk is read 272 KiB of fragments and
+// written 64 KiB of weights (2600 cycles at 128 bytes a cycle), beside 2048
+// cycles of matrix instructions a SIMD. Measured per call, request table
+// included, against one wave per SIMD that kept H in its registers (as many
+// LDS reads, nothing to overlap them): 64 requests, 64,324 candidates, 256 ->
+// 512 -> 256: 53.5 -> 49.3 us; 9 requests, 6,025 candidates, 128 -> 960 ->
+// 256: 33.4 -> 24.5 us; one request of 500: 24.7 -> 21.5 us. Four waves of 64
+// candidates (a third fewer LDS reads, 400 registers) copy operands through
+// the accumulation registers: 99 us. Without the DMA: 46 us.
 //
 // Matrix-core roles (32x32x16 bf16 MFMA): both products are computed
 // transposed, hidden / output units on the M side and candidates on the N
 // side, so that a lane's accumulator holds one candidate's runs of four
 // consecutive units:
 //   H^T[h][n]  = sum_k W1_CC[h][k] X^C[n][k]    A = W1 rows (LDS), B = X^C rows
-//   Y^T[o][n] += sum_h W2[o][h] H[n][h]         A = W2 rows (LDS), B = H
-// One half-wave swap turns the H^T accumulator layout into the B operand of
-// the second product (eight consecutive hidden units per lane), and the same
-// swap gives 16 contiguous output bytes per lane for the stores.
+//   Y^T[o][n] += sum_h W2[o][h] H[n][h]         A = W2 rows (LDS), B = H (LDS)
+// One half-wave swap gives 16 contiguous bytes per lane of H and of the output.
 //
-// Tiles cover the candidates contiguously; the Zb rows of two consecutive
-// requests are staged per tile, and each candidate picks its own. A tile
-// that spans more than two requests (requests of fewer than 128 candidates)
-// is run once per pair of requests, storing only that pair's rows.
+// Tiles cover the candidates contiguously, whatever requests they belong to.
 #include "common.h"
 #include "kernels.h"
 #include "launch.h"
 
-#include <climits>
-
 namespace rocs {
 namespace {
 
-constexpr int kMlpBM = 128;          // candidates per tile (4 waves x 32)
+constexpr int kMlpBM = 128;          // candidates per tile
 constexpr int kMlpHC = 64;           // hidden units per chunk
-constexpr int kMlpMaxHidden = 1024;  // two Zb rows per tile, double-buffered in LDS
+constexpr int kMlpMaxHidden = 1024;
 
 // Chunk position of 16-byte chunk c of an LDS row: c ^ swizzle(row). With
 // 16 or more chunks per row the 16 rows read by a quarter-wave at one chunk
@@ -89,42 +92,8 @@ __device__ __forceinline__ int owner_scalar(const __attribute__((address_space(4
   return lo;
 }
 
-// One unit of work: tile t, pass p (the p-th pair of the tile's requests).
-struct MlpItem {
-  int t, p, passes;
-  int64_t n0;
-  int rows;
-  int r0, r1;          // the pair's Zb rows
-  int lo, mid, hi;     // candidates [lo, mid) belong to r0, [mid, hi) to r0 + 1
-};
-
-__device__ __forceinline__ MlpItem mlp_item(const __attribute__((address_space(4))) int32_t* off,
-                                            int R, int64_t N, int t, int p) {
-  MlpItem it;
-  it.t = t;
-  it.p = p;
-  it.n0 = (int64_t)t * kMlpBM;
-  it.rows = (int)min((int64_t)kMlpBM, N - it.n0);
-  if (off != nullptr) {
-    const int ra = owner_scalar(off, R, it.n0);
-    const int rb = owner_scalar(off, R, it.n0 + it.rows - 1);
-    it.passes = (rb - ra) / 2 + 1;
-    it.r0 = ra + 2 * p;
-    it.r1 = min(it.r0 + 1, R - 1);
-    it.lo = off[it.r0];
-    it.mid = off[it.r0 + 1];
-    it.hi = off[min(it.r0 + 2, R)];
-  } else {
-    it.passes = 1;
-    it.r0 = it.r1 = 0;
-    it.lo = 0;
-    it.mid = it.hi = INT_MAX;
-  }
-  return it;
-}
-
 template <int KC, int DO>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void ikbo_mlp2_bf16(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1,
                     const float* __restrict__ zb, int64_t zb_stride,
                     const bf16_t* __restrict__ w2, const float* __restrict__ b2,
@@ -133,20 +102,18 @@ void ikbo_mlp2_bf16(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1,
   constexpr int BM = kMlpBM, HC = kMlpHC;
   constexpr int ROWB1 = 2 * KC;                 // bytes of one W1 row
   constexpr int CPR1 = ROWB1 / 16;              // its 16-byte chunks
-  constexpr int ROWB2 = 2 * HC;                 // bytes of one W2 row segment (128)
+  constexpr int ROWB2 = 2 * HC;                 // bytes of one W2 (or H) row segment (128)
   constexpr int W1B = HC * ROWB1;               // W1 part of a ring slot
   constexpr int W2B = DO * ROWB2;               // W2 part of a ring slot
-  constexpr int SLOT = W1B + W2B;
-  constexpr int ZBUF = 2 * 4 * kMlpMaxHidden;   // two Zb rows (fp32), one buffer
-  constexpr int ZBO = 2 * SLOT;                 // Zb rows, two buffers (by item parity)
-  constexpr int B2O = ZBO + 2 * ZBUF;           // b2 (fp32)
+  constexpr int W2O = 2 * W1B;                  // W2 slots after the two W1 slots
+  constexpr int HO = W2O + 2 * W2B;             // H of a chunk, [candidate][64], two buffers
+  constexpr int HB = BM * ROWB2;
   constexpr int KS = KC / 16;                   // k-steps of the first product
-  constexpr int OB = DO / 32;                   // 32-unit output blocks
+  constexpr int OBW = DO / 128;                 // 32-unit output blocks per wave
   constexpr int I1 = W1B / 1024, I2 = W2B / 1024;   // wave-wide DMA loads per chunk
-  static_assert(I1 % 4 == 0 && I2 % 4 == 0, "chunk loads split over four waves");
-  static_assert(DO * 4 <= 1024, "b2 staging");
-  static_assert(B2O + 1024 <= 160 * 1024, "LDS");
-  __shared__ __attribute__((aligned(1024))) char lds[B2O + 1024];
+  static_assert(I1 % 8 == 0 && I2 % 8 == 0, "chunk loads split over eight waves");
+  static_assert(HO + 2 * HB <= 160 * 1024, "LDS");
+  __shared__ __attribute__((aligned(1024))) char lds[HO + 2 * HB];
   ROCS_LDS char* const lds3 = (ROCS_LDS char*)lds;
   // The offsets are read-only for the kernel's lifetime: scalar loads.
   const __attribute__((address_space(4))) int32_t* off =
@@ -155,197 +122,239 @@ void ikbo_mlp2_bf16(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
-  const int row = 32 * wave + l32;              // this lane's candidate within the tile
+  const int hb = wave & 1, cb = wave >> 1;      // first product: hidden and candidate block
+  const int og = wave & 3, cg = wave >> 2;      // second: output quarter, candidate half
+  const int row = 32 * cb + l32;                // this lane's candidate (first product)
   const int n_tiles = (int)((N + BM - 1) / BM);
-  const int G = (int)gridDim.x;
   const uint32_t lbase = lds_addr(lds);
 
-  // Chunk c of the weights into ring slot `slot`: W1 rows 64 c .. 64 c + 63
-  // (contiguous in memory), and W2 columns 64 c .. 64 c + 63 of every output
-  // row. Load i of the chunk fills 1 KiB of the slot in lane order.
-  auto issue_chunk = [&](int c, int slot) __attribute__((always_inline)) {
-    const uint32_t dst = lbase + (uint32_t)(slot * SLOT);
+  // Chunk c of W1 (rows 64 c .. 64 c + 63, contiguous in memory) and of W2
+  // (columns 64 c .. 64 c + 63 of every output row) into their ring slots.
+  // Load i of the chunk fills 1 KiB of the slot in lane order.
+  auto issue_w1 = [&](int c, int slot) __attribute__((always_inline)) {
     const char* s1 = reinterpret_cast<const char*>(w1 + (int64_t)c * HC * KC);
 #pragma unroll
-    for (int j = 0; j < I1 / 4; ++j) {
-      const int i = wave + 4 * j, p = 64 * i + lane;
+    for (int j = 0; j < I1 / 8; ++j) {
+      const int i = wave + 8 * j, p = 64 * i + lane;
       const int r = p / CPR1, pos = p % CPR1;
       lds_dma16_sv(s1, (uint32_t)(r * ROWB1 + 16 * (pos ^ mlp_swizzle<CPR1>(r))),
-                   dst + 1024u * i);
+                   lbase + (uint32_t)(slot * W1B) + 1024u * i);
     }
+  };
+  auto issue_w2 = [&](int c, int slot) __attribute__((always_inline)) {
     const char* s2 = reinterpret_cast<const char*>(w2 + (int64_t)c * HC);
 #pragma unroll
-    for (int j = 0; j < I2 / 4; ++j) {
-      const int i = wave + 4 * j, p = 64 * i + lane;
+    for (int j = 0; j < I2 / 8; ++j) {
+      const int i = wave + 8 * j, p = 64 * i + lane;
       const int o = p >> 3, pos = p & 7;
       lds_dma16_sv(s2, (uint32_t)(o * DH * 2 + 16 * (pos ^ mlp_swizzle<8>(o))),
-                   dst + (uint32_t)W1B + 1024u * i);
+                   lbase + (uint32_t)(W2O + slot * W2B) + 1024u * i);
     }
   };
-  // The item's two Zb rows into Zb buffer `buf` (lanes past the rows repeat
-  // the last piece, into the buffer's padding).
-  auto issue_zb = [&](const MlpItem& it, int buf) __attribute__((always_inline)) {
-    const char* zs = reinterpret_cast<const char*>(zb + (int64_t)it.r0 * zb_stride);
-    const int per_row = DH / 4, pieces = 2 * per_row;
-    const uint32_t r1off = (uint32_t)((int64_t)(it.r1 - it.r0) * zb_stride * 4);
-    for (int i = wave; 64 * i < pieces; i += 4) {
-      const int p = min(64 * i + lane, pieces - 1);
-      const uint32_t src = (p < per_row ? 0u : r1off) + 16u * (uint32_t)(p % per_row);
-      lds_dma16_sv(zs, src, lbase + (uint32_t)(ZBO + buf * ZBUF) + 1024u * i);
-    }
-  };
-  auto load_x = [&](const MlpItem& it, bf16x8 (&xf)[KS]) __attribute__((always_inline)) {
-    const int xrow = min(row, it.rows - 1);        // clamped; extra rows never stored
-    const bf16_t* xp = x + (it.n0 + xrow) * KC + 8 * hh;
+  // This lane's candidate rows of tile t as B fragments (row l32 of the block,
+  // features 16 s + 8 hh ..); rows past the end are clamped, never stored.
+  bf16x8 xf[KS];
+  auto load_x = [&](int t) __attribute__((always_inline)) {
+    const int64_t n = min((int64_t)t * BM + row, N - 1);
+    const bf16_t* xp = x + n * KC + 8 * hh;
 #pragma unroll
     for (int s = 0; s < KS; ++s) xf[s] = *reinterpret_cast<const bf16x8*>(xp + 16 * s);
   };
-
-  // Prologue: the first item's Zb rows and b2 (zeros when absent), the first
-  // weight chunk, and the wave's 32 candidate rows as B fragments (lane:
-  // row l32, features 16 s + 8 hh ..).
-  MlpItem cur = mlp_item(off, R, N, (int)blockIdx.x, 0);
-  if (zb != nullptr) {
-    issue_zb(cur, 0);
-  } else {
-    for (int i = tid; i < 2 * ZBUF / 16; i += 256)
-      *reinterpret_cast<ROCS_LDS u32x4*>(lds3 + ZBO + 16 * i) = u32x4{0u, 0u, 0u, 0u};
-  }
-  if (b2 != nullptr) {
-    if (wave == 1) lds_dma16_sv(b2, (uint32_t)(16 * min(lane, DO / 4 - 1)), lbase + (uint32_t)B2O);
-  } else if (tid < DO / 4) {
-    *reinterpret_cast<ROCS_LDS u32x4*>(lds3 + B2O + 16 * tid) = u32x4{0u, 0u, 0u, 0u};
-  }
-  issue_chunk(0, 0);
-  bf16x8 xf[KS], xn[KS];
-  load_x(cur, xf);
-  // Make the fragments resident here: the chunk loop then has only the
-  // ring's DMA loads in flight, which the compiler does not count, so it
-  // places no waits of its own there.
+  // The Zb row of this lane's candidate: one scalar search per tile, then a
+  // walk over the tile's request boundaries (a tile of many small requests
+  // searches per lane instead).
+  auto find_request = [&](int t) __attribute__((always_inline)) -> const float* {
+    if (off == nullptr) return zb;
+    const int64_t n0 = (int64_t)t * BM, last = min(n0 + BM, N) - 1, n = min(n0 + row, last);
+    int r = owner_scalar(off, R, n0);
+    int at = r, steps = 0;
+    for (; at + 1 < R && (int64_t)off[at + 1] <= last && steps < 8; ++steps) {
+      ++at;
+      if (n >= (int64_t)off[at]) r = at;
+    }
+    if (steps == 8) r = owner_of(off_g, R, n);
+    return zb + (int64_t)r * zb_stride;
+  };
+  const float* zrow;
+  // The first product's accumulators start at units 64 c + 32 hb + 8 q + 4 hh
+  // .. + 3 of that row. Loaded straight into them, between the packing of one
+  // chunk's H and the next chunk's products, while the second product runs
+  // (a second register set, loaded a whole chunk ahead, was no faster).
+  f32x16 acc1;
+  auto load_z = [&](int c) __attribute__((always_inline)) {
+    if (zb == nullptr) {
+      acc1 = f32x16{};
+      return;
+    }
 #pragma unroll
-  for (int s = 0; s < KS; ++s) asm volatile("" :: "v"(as_u32x4(xf[s])));
-  wait_vmcnt<0>();
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 z = *reinterpret_cast<const f32x4*>(zrow + HC * c + 32 * hb + 8 * q + 4 * hh);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc1[4 * q + i] = z[i];
+    }
+  };
+
+  int t = (int)blockIdx.x;
+  issue_w1(0, 0);
+  load_x(t);
+  zrow = find_request(t);
+  load_z(0);
+  // Make the candidate rows resident here: the compiler does not count the
+  // DMA loads, so its own waits for them would include the DMA issued later.
+  auto resident = [&]() __attribute__((always_inline)) {
+    wait_vmcnt<0>();
+#pragma unroll
+    for (int s = 0; s < KS; ++s) asm volatile("" :: "v"(as_u32x4(xf[s])));
+  };
+  resident();
   ring_barrier();
 
   // Fragment addresses: row l32 of a 32-row block, chunk 2 s + hh; the
   // swizzle turns the s step into an XOR with 32 s.
-  const uint32_t fa1 = (uint32_t)(l32 * ROWB1 + 16 * (hh ^ mlp_swizzle<CPR1>(l32)));
-  const uint32_t fa2 = (uint32_t)(l32 * ROWB2 + 16 * (hh ^ mlp_swizzle<8>(l32)));
+  const uint32_t fa1 = (uint32_t)((32 * hb + l32) * ROWB1 + 16 * (hh ^ mlp_swizzle<CPR1>(l32)));
+  const uint32_t f2 = (uint32_t)(l32 * ROWB2 + 16 * (hh ^ mlp_swizzle<8>(l32)));
+  const uint32_t fa2 = (uint32_t)(W2O + 32 * OBW * og * ROWB2) + f2;
+  const uint32_t fh = (uint32_t)(HO + 64 * cg * ROWB2) + f2;
   const float lo1 = relu1 ? 0.f : -INFINITY, lo2 = relu2 ? 0.f : -INFINITY;
   const int nch = DH / HC;
-  int slot = 0, zbuf = 0;
-  while (true) {
-    // The next item, found while this one computes (scalar loads).
-    const bool more = cur.p + 1 < cur.passes;
-    const MlpItem nxt = mlp_item(off, R, N, more ? cur.t : cur.t + G, more ? cur.p + 1 : 0);
-    const bool live = nxt.t < n_tiles;
-    // This lane's candidate: its request's Zb row within the buffer.
-    const int64_t n = cur.n0 + row;
-    const uint32_t zrow = (uint32_t)(ZBO + zbuf * ZBUF + (n >= cur.mid ? 4 * DH : 0));
-    f32x16 acc2[OB];
+  f32x16 acc2[OBW][2];
+  // First product of the chunk in W1 slot `par`, on top of acc1; W1 fragments
+  // three k-steps ahead.
+  auto first = [&](int par) __attribute__((always_inline)) {
+    const uint32_t sl = (uint32_t)(par * W1B);
+    bf16x8 af[4];
+    auto load_a = [&](int s) __attribute__((always_inline)) {
+      af[s % 4] = *reinterpret_cast<const ROCS_LDS bf16x8*>(lds3 + sl + (fa1 ^ (32u * s)));
+    };
+    load_a(0);
+    load_a(1);
+    load_a(2);
 #pragma unroll
-    for (int ob = 0; ob < OB; ++ob)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc2[ob][e] = 0.f;
-
-    for (int c = 0; c < nch; ++c) {
-      const bool last = c + 1 == nch;
-      if (!last || live) issue_chunk(last ? 0 : c + 1, slot ^ 1);
-      if (last && live) {
-        if (zb != nullptr) issue_zb(nxt, zbuf ^ 1);
-        load_x(nxt, xn);
-      }
-      const uint32_t s1 = (uint32_t)(slot * SLOT), s2 = s1 + (uint32_t)W1B;
-      // H^T of the chunk (two 32-unit blocks); W1 fragments two k-steps ahead.
-      bf16x8 af[3][2];
-      auto load_a = [&](int s, int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          af[buf][b] = *reinterpret_cast<const ROCS_LDS bf16x8*>(
-              lds3 + s1 + 32 * b * ROWB1 + (fa1 ^ (32u * s)));
-      };
-      load_a(0, 0);
-      load_a(1, 1);
-      f32x16 acc1[2];
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc1[b][e] = 0.f;
-#pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        if (s + 2 < KS) load_a(s + 2, (s + 2) % 3);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc1[b] = mfma32(af[s % 3][b], xf[s], acc1[b]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      // The second product's first W2 fragments and the chunk's Zb values are
-      // read while the epilogue of the first runs.
-      bf16x8 wf[2][OB];
-      auto load_w = [&](int s, int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int ob = 0; ob < OB; ++ob)
-          wf[buf][ob] = *reinterpret_cast<const ROCS_LDS bf16x8*>(
-              lds3 + s2 + 32 * ob * ROWB2 + (fa2 ^ (32u * s)));
-      };
-      f32x4 z[2][4];
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          z[b][q] = *reinterpret_cast<const ROCS_LDS f32x4*>(
-              lds3 + zrow + 4 * (HC * c + 32 * b + 8 * q + 4 * hh));
-      load_w(0, 0);
-      // Zb, activation, bf16: the B operands of the second product, one per
-      // 16-unit k-step (lane: candidate l32, hidden units 16 s + 8 hh ..).
-      u32x4 hb[4];
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        uint32_t p[4][2];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) pack4(acc1[b], q, z[b][q], lo1, p[q][0], p[q][1]);
-        hb[2 * b] = swap_halves(p, 0);
-        hb[2 * b + 1] = swap_halves(p, 1);
-      }
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        if (s + 1 < 4) load_w(s + 1, (s + 1) & 1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int ob = 0; ob < OB; ++ob)
-          acc2[ob] = mfma32(wf[s & 1][ob], as_bf16x8(hb[s]), acc2[ob]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      wait_vmcnt<0>();          // the next chunk (and the next item's rows) resident
-      ring_barrier();           // every wave's loads in, this slot free
-      slot ^= 1;
+    for (int s = 0; s < KS; ++s) {
+      if (s + 3 < KS) load_a(s + 3);
+      __builtin_amdgcn_sched_barrier(0);
+      acc1 = mfma32(af[s % 4], xf[s], acc1);
+      __builtin_amdgcn_sched_barrier(0);
     }
-
-    // Epilogue: b2, activation, bf16; after the swap each lane stores 16
-    // contiguous bytes (outputs 32 ob + 16 s + 8 hh ..) of its candidate,
-    // if it belongs to this item's pair of requests.
-    const bool store = row < cur.rows && n >= cur.lo && n < cur.hi;
-    bf16_t* op = out + n * DO + 8 * hh;
+  };
+  // Activation, bf16, into H buffer `par`.
+  auto put_h = [&](int par) __attribute__((always_inline)) {
+    uint32_t p[4][2];
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ob = 0; ob < OB; ++ob) {
-      uint32_t p[4][2];
+    for (int q = 0; q < 4; ++q) pack4(acc1, q, zero, lo1, p[q][0], p[q][1]);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      *reinterpret_cast<ROCS_LDS u32x4*>(
+          lds3 + HO + par * HB + row * ROWB2 + 16 * ((4 * hb + 2 * s + hh) ^ mlp_swizzle<8>(row))) =
+          swap_halves(p, s);
+  };
+  // Second product of the chunk in W2 slot and H buffer `par`.
+  bf16x8 wf[2][OBW], hf[2][2];
+  auto load_2 = [&](int par, int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ob = 0; ob < OBW; ++ob)
+      wf[s & 1][ob] = *reinterpret_cast<const ROCS_LDS bf16x8*>(
+          lds3 + par * W2B + 32 * ob * ROWB2 + (fa2 ^ (32u * s)));
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      hf[s & 1][j] = *reinterpret_cast<const ROCS_LDS bf16x8*>(
+          lds3 + par * HB + 32 * j * ROWB2 + (fh ^ (32u * s)));
+  };
+  auto second = [&](int par) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if (s + 1 < 4) load_2(par, s + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ob = 0; ob < OBW; ++ob)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc2[ob][j] = mfma32(wf[s & 1][ob], hf[s & 1][j], acc2[ob][j]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  int par = 0;                   // ring slot and H buffer of the chunk in the first product
+  while (true) {
+    const int tn = t + (int)gridDim.x;
+    const bool live = tn < n_tiles;
+    // Chunk 0: its first product alone. W1 of the next chunk and W2 of this
+    // one load meanwhile.
+    issue_w2(0, par);
+    if (nch > 1 || live) issue_w1(nch > 1 ? 1 : 0, par ^ 1);
+#pragma unroll
+    for (int ob = 0; ob < OBW; ++ob)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const f32x4 bb = *reinterpret_cast<const ROCS_LDS f32x4*>(
-            lds3 + B2O + 4 * (32 * ob + 8 * q + 4 * hh));
-        pack4(acc2[ob], q, bb, lo2, p[q][0], p[q][1]);
-      }
+        f32x4 b = {0.f, 0.f, 0.f, 0.f};
+        if (b2 != nullptr)
+          b = *reinterpret_cast<const f32x4*>(b2 + 32 * (OBW * og + ob) + 8 * q + 4 * hh);
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const u32x4 v = swap_halves(p, s);
-        if (store) *reinterpret_cast<u32x4*>(op + 32 * ob + 16 * s) = v;
+        for (int i = 0; i < 4; ++i) acc2[ob][0][4 * q + i] = acc2[ob][1][4 * q + i] = b[i];
       }
+    const float* znext = live ? find_request(tn) : zb;   // in this light interval
+    first(par);
+    put_h(par);
+    if (nch > 1) load_z(1);
+    wait_lgkmcnt0();
+    wait_vmcnt<0>();
+    ring_barrier();
+    par ^= 1;
+    // Chunk c's first product with chunk c - 1's second: one barrier a chunk.
+    for (int c = 1; c < nch; ++c) {
+      const bool last = c + 1 == nch;
+      issue_w2(c, par);
+      if (!last || live) issue_w1(last ? 0 : c + 1, par ^ 1);
+      first(par);
+      load_2(par ^ 1, 0);
+      put_h(par);
+      if (!last) load_z(c + 1);
+      second(par ^ 1);
+      wait_lgkmcnt0();
+      wait_vmcnt<0>();          // the next chunk's W1, this one's W2, the next Zb values
+      ring_barrier();           // every wave's loads in, H complete, the other slots free
+      par ^= 1;
     }
-    if (!live) break;
-    cur = nxt;
-    zbuf ^= 1;
+    // The last chunk's second product; the next tile's rows load meanwhile
+    // (the candidate registers are free).
+    if (live) {
+      load_x(tn);
+      zrow = znext;
+      load_z(0);
+    }
+    load_2(par ^ 1, 0);
+    second(par ^ 1);
+
+    // Epilogue: activation, bf16; after the swaps four lanes store 64
+    // contiguous bytes of one candidate.
+    const int l16 = lane & 15, q4 = lane >> 4;
+    const int64_t n0 = (int64_t)t * BM + 64 * cg + l16;
+    bf16_t* op = out + n0 * DO + 32 * OBW * og + 16 * (q4 & 1) + 8 * hh;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) xf[s] = xn[s];
+    for (int ob = 0; ob < OBW; ++ob)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        uint32_t p[4][2];
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) pack4(acc2[ob][j], q, zero, lo2, p[q][0], p[q][1]);
+        const u32x4 s0 = swap_halves(p, 0), s1 = swap_halves(p, 1);
+        u32x4 o[2];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const auto w = __builtin_amdgcn_permlane16_swap(s0[e], s1[e], false, false);
+          o[0][e] = w[0];
+          o[1][e] = w[1];
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          if (n0 + 32 * j + 16 * i < N)
+            *reinterpret_cast<u32x4*>(op + (int64_t)(32 * j + 16 * i) * DO + 32 * ob) = o[i];
+      }
+    if (!live) break;
+    resident();
+    ring_barrier();             // every wave is past the last chunk's W2 and H
+    t = tn;
   }
 }
 
@@ -357,7 +366,7 @@ hipError_t launch_fused(const Mlp2Args& a, const float* zb, int64_t zb_stride,
   if (e != hipSuccess) return e;
   const int64_t tiles = (a.N + kMlpBM - 1) / kMlpBM;
   const int grid = (int)(tiles < cus ? tiles : cus);
-  return launch_kernel(ikbo_mlp2_bf16<KC, DO>, dim3((uint32_t)grid), dim3(256), s,
+  return launch_kernel(ikbo_mlp2_bf16<KC, DO>, dim3((uint32_t)grid), dim3(512), s,
                        static_cast<const bf16_t*>(a.x_cand),
                        static_cast<const bf16_t*>(a.w1_cand), zb, zb_stride,
                        static_cast<const bf16_t*>(a.w2), a.b2, off, (int)a.R, a.N,
@@ -368,8 +377,7 @@ hipError_t launch_fused(const Mlp2Args& a, const float* zb, int64_t zb_stride,
 }  // namespace
 
 bool mlp2_fused_shape(int64_t R, int64_t k_cand, int64_t d_hidden, int64_t d_out) {
-  // The second Zb row of a tile is addressed by a 32-bit byte offset from
-  // the first: the request table must stay under 4 GiB.
+  // Request tables of 4 GiB and more take the two-launch form.
   return (k_cand == 128 || k_cand == 256) && (d_out == 128 || d_out == 256) &&
          d_hidden >= kMlpHC && d_hidden % kMlpHC == 0 && d_hidden <= kMlpMaxHidden &&
          R * d_hidden * 4 < (int64_t(1) << 32);
