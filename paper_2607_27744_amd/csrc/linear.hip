@@ -37,10 +37,14 @@ __global__ __launch_bounds__(256) void request_ids_kernel(const int32_t* __restr
 // the request-side output Y^R = act(X^R W_RR^T + b^R) (bf16) from the same
 // launch: the stacked weight [W_RR; W_CR] of Section 4.1, one GEMM at batch
 // size R. One workgroup per 16 x 16 output tile (the W_RR column tiles come
-// first); its four waves split K in 32-wide steps (operands straight from
+// first); its eight waves split K in 32-wide steps (operands straight from
 // global memory into MFMA registers, each lane's 8 consecutive k are one
-// 16-byte load) and reduce through LDS in a fixed order. Workgroups past the
-// tiles expand the index map when the candidate GEMM needs it.
+// 16-byte load) and reduce through LDS in a fixed order. A handful of
+// workgroups at batch size R is bound by the latency of a wave's loads: with
+// eight waves and eight steps in flight a K of 2048 is one round trip to L2
+// (16 requests, 1024 outputs: 7 us), where four waves with four steps in
+// flight made four (12 us); a K of 4096, 1024 outputs: 22 -> 12 us. Workgroups past the tiles expand the index map when the
+// candidate GEMM needs it.
 // ---------------------------------------------------------------------------
 struct RequestOut {          // the optional Y^R part of the stacked weight
   const bf16_t* w;           // W_RR [d, K]
@@ -49,8 +53,11 @@ struct RequestOut {          // the optional Y^R part of the stacked weight
   int d, tiles, relu;        // tiles = ceil(d / 16); 0 when there is no Y^R
 };
 
-// One 16 x 16 output tile `tile` of the stacked request GEMM, by a 256-thread
-// workgroup; `red` is 4 KiB of LDS. Returns whether the tile was a Zb tile
+constexpr int kReqAhead = 8;   // k-steps of a wave in flight
+constexpr int kReqMaxBlocks = 1 << 22;   // workgroups of 512 per launch; they loop over more tiles
+
+// One 16 x 16 output tile `tile` of the stacked request GEMM, by a 512-thread
+// workgroup; `red` is 8 KiB of LDS. Returns whether the tile was a Zb tile
 // (the candidate side's input) and, for wave 0, its (row block, column block).
 __device__ __forceinline__ bool request_tile(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w_in,
@@ -69,22 +76,26 @@ __device__ __forceinline__ bool request_tile(
   const bool dok = d0 + row < D, rok = r0 + row < R;
   const bf16_t* wp = w + (int64_t)(d0 + row) * K + kq;
   const bf16_t* xp = x + (int64_t)(r0 + row) * K + kq;
-  // Four waves split K; in a larger workgroup (the streaming kernel's) the
-  // other waves only join the barriers, so both launch forms sum alike.
-  if (wave < 4) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int k = wave * 32; k < K; k += 128) {
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int k0 = wave * 32; k0 < K; k0 += 256 * kReqAhead) {
+    u32x4 a[kReqAhead], b[kReqAhead];
+#pragma unroll
+    for (int j = 0; j < kReqAhead; ++j) {
+      const int k = k0 + 256 * j;
       const bool kok = k + kq < K;
-      const bf16x8 a = as_bf16x8(load16(wp + k, dok && kok));
-      const bf16x8 b = as_bf16x8(load16(xp + k, rok && kok));
-      acc = mfma16(a, b, acc);   // acc[i] = Z[r0 + row][d0 + 4 (lane / 16) + i]
+      a[j] = load16(wp + k, dok && kok);
+      b[j] = load16(xp + k, rok && kok);
     }
-    red[wave * kWave + lane] = acc;
+#pragma unroll
+    for (int j = 0; j < kReqAhead; ++j)   // acc[i] = Z[r0 + row][d0 + 4 (lane / 16) + i]
+      if (k0 + 256 * j < K) acc = mfma16(as_bf16x8(a[j]), as_bf16x8(b[j]), acc);
   }
+  red[wave * kWave + lane] = acc;
   __syncthreads();
   if (wave == 0) {
-    f32x4 s = ((red[lane] + red[kWave + lane]) + red[2 * kWave + lane]) + red[3 * kWave + lane];
+    f32x4 s = red[lane];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) s += red[w * kWave + lane];
     const int d = d0 + (lane >> 4) * 4;
     if (rok && d < D) {
       if (bias != nullptr) s += *reinterpret_cast<const f32x4*>(bias + d);
@@ -100,17 +111,20 @@ __device__ __forceinline__ bool request_tile(
   return !to_y;
 }
 
-__global__ __launch_bounds__(256) void request_gemm_bf16(
+__global__ __launch_bounds__(512) void request_gemm_bf16(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w_in, const float* __restrict__ bias_in,
     float* __restrict__ z, const int32_t* __restrict__ off, int32_t* __restrict__ ids, int R,
-    int64_t N, int K, int D_in, int tiles_d, int z_blocks, RequestOut yr) {
+    int64_t N, int K, int D_in, int tiles_d, int z_tiles, int z_blocks, RequestOut yr) {
   if ((int)blockIdx.x >= z_blocks) {
-    const int64_t n = (int64_t)(blockIdx.x - z_blocks) * 256 + threadIdx.x;
+    const int64_t n = (int64_t)(blockIdx.x - z_blocks) * 512 + threadIdx.x;
     if (n < N) ids[n] = owner_of(off, R, n);
     return;
   }
-  __shared__ f32x4 red[4 * kWave];
-  request_tile(x, w_in, bias_in, z, R, K, D_in, tiles_d, yr, (int)blockIdx.x, (ROCS_LDS f32x4*)red);
+  __shared__ f32x4 red[8 * kWave];
+  for (int t = (int)blockIdx.x; t < z_tiles; t += z_blocks) {
+    request_tile(x, w_in, bias_in, z, R, K, D_in, tiles_d, yr, t, (ROCS_LDS f32x4*)red);
+    __syncthreads();                      // red is free for the next tile
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -648,7 +662,7 @@ void ikbo_gemm_stream(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w
     }
     // Workgroup-wide verdicts go through one LDS word past the reduction
     // area, so every wave takes the same branch around the tiles' barriers.
-    ROCS_LDS int* const verdict = (ROCS_LDS int*)(lds3 + BBASE + 2 * SLAB + 4096);
+    ROCS_LDS int* const verdict = (ROCS_LDS int*)(lds3 + BBASE + 2 * SLAB + 8192);
     if (threadIdx.x == 0) *verdict = 0;
     __syncthreads();
     if (lane == 0 && spins == kFlagSpinLimit) *verdict = 1;
@@ -1024,11 +1038,12 @@ hipError_t launch_request_table(const LinearArgs& a, hipStream_t s) {
   const int tiles_d = (int)((a.d_out + 15) / 16);
   if (!grid_fits((int64_t)tiles_d * ((a.R + 15) / 16), 256)) return hipErrorInvalidConfiguration;
   const int req_tiles = tiles_d * (int)((a.R + 15) / 16);
+  const int z_blocks = req_tiles < kReqMaxBlocks ? req_tiles : kReqMaxBlocks;
   const RequestOut none{nullptr, nullptr, nullptr, 0, 0, 0};
-  return launch_kernel(request_gemm_bf16, dim3(req_tiles), dim3(256), s,
+  return launch_kernel(request_gemm_bf16, dim3(z_blocks), dim3(512), s,
                        static_cast<const bf16_t*>(a.x_req), static_cast<const bf16_t*>(a.w_req),
                        a.bias, a.z, a.cand_offsets, a.ids, (int)a.R, a.N, (int)a.k_req,
-                       (int)a.d_out, tiles_d, req_tiles, none);
+                       (int)a.d_out, tiles_d, req_tiles, z_blocks, none);
 }
 
 hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
@@ -1067,12 +1082,13 @@ hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
     return hipErrorInvalidConfiguration;
   const int req_tiles = (yr.tiles + tiles_d) * (int)((a.R + 15) / 16);
   if (a.k_req > 0 && !fused) {
-    const int id_blocks = stream || a.ids_given ? 0 : (int)((a.N + 255) / 256);
-    hipError_t e = launch_kernel(request_gemm_bf16, dim3(req_tiles + id_blocks), dim3(256), s,
+    const int id_blocks = stream || a.ids_given ? 0 : (int)((a.N + 511) / 512);
+    const int z_blocks = req_tiles < kReqMaxBlocks ? req_tiles : kReqMaxBlocks;
+    hipError_t e = launch_kernel(request_gemm_bf16, dim3(z_blocks + id_blocks), dim3(512), s,
                                  static_cast<const bf16_t*>(a.x_req),
                                  static_cast<const bf16_t*>(a.w_req), a.bias, a.z,
                                  a.cand_offsets, a.ids, (int)a.R, a.N, (int)a.k_req,
-                                 (int)a.d_out, tiles_d, req_tiles, yr);
+                                 (int)a.d_out, tiles_d, req_tiles, z_blocks, yr);
     if (e != hipSuccess) return e;
   }
   if (a.N == 0) return hipSuccess;      // request-side output only
