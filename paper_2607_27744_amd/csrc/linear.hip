@@ -127,163 +127,254 @@ __global__ __launch_bounds__(512) void request_gemm_bf16(
   }
 }
 
-// ---------------------------------------------------------------------------
-// Candidate-side GEMM with the fused request broadcast, bf16 MFMA 32x32x16.
-//
-// Matrix-core roles: A = W_CC rows (output features d), B = candidate rows,
-// so each lane's accumulator holds, for one candidate, four runs of 4
-// consecutive output features (8-byte bf16 stores). Workgroup tile BM
-// (features) x BN (candidates), WAVES_M x WAVES_N waves, K staged through
-// double-buffered LDS in BK-wide slabs; the next slab is prefetched into
-// registers while the current one feeds the MFMAs. LDS rows carry a 16-byte
-// pad so the rows read by one fragment load spread over all banks.
-//
-// Epilogue fusion: accumulators are initialised with Z[m_n][d] + b[d] before
-// the K loop (so these loads overlap the first slab's loads), and the
-// epilogue only applies the activation, rounds and stores. A tile whose rows
-// all belong to one request (the common case: requests hold hundreds to tens
-// of thousands of candidates) loads each Z row segment once for all its rows.
-// ---------------------------------------------------------------------------
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool HAS_ADD>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) __attribute__((amdgpu_waves_per_eu(2)))
-void ikbo_gemm_bf16(
-    const bf16_t* __restrict__ x, const bf16_t* __restrict__ xadd, const bf16_t* __restrict__ w,
-    const float* __restrict__ bias, const float* __restrict__ z, const int32_t* __restrict__ ids,
-    bf16_t* __restrict__ out, int64_t N, int K, int D, int tiles_m, int relu, int R,
-    int ids_sorted) {
-  constexpr int NT = 64 * WAVES_M * WAVES_N;
-  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-  constexpr int FM = WM / 32, FN = WN / 32;
-  constexpr int ROW = BK + 8;                 // LDS row (bf16) with 16-byte pad
-  constexpr int CPR = BK / 8;                 // 16-byte chunks per slab row
-  constexpr int RPP = NT / CPR;               // slab rows staged per pass
-  constexpr int CA = BM / RPP, CB = BN / RPP;
-  static_assert(BM % RPP == 0 && BN % RPP == 0, "staging does not tile");
-  static_assert(WM % 32 == 0 && WN % 32 == 0 && BK % 16 == 0, "MFMA tiling");
-  __shared__ __attribute__((aligned(16))) bf16_t lds_a[2][BM][ROW];
-  __shared__ __attribute__((aligned(16))) bf16_t lds_b[2][BN][ROW];
+// ReLU of two packed bf16 values: as 16-bit integers the negative values
+// (sign bit set) are exactly those below zero, so a packed integer max with
+// zero clamps them (and -0) to +0. Written as the one instruction: the
+// compiler's own lowering of a packed max on a bit-cast pair has been seen
+// to drop the second word of the pair.
+__device__ __forceinline__ uint32_t relu_bf16x2(uint32_t p) {
+  uint32_t r;
+  asm("v_pk_max_i16 %0, %1, 0" : "=v"(r) : "v"(p));
+  return r;
+}
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// ---------------------------------------------------------------------------
+// Tiled candidate GEMM, bf16 MFMA 32x32x16: any map, any K and D of the fast
+// path (multiples of 8 and 4), the pointwise residual input, and calls too
+// small for the streaming kernel below.
+//
+// Matrix-core roles: A = W_CC rows (output features d), B = candidate rows, so
+// each lane's accumulator holds, for one candidate, four runs of 4 consecutive
+// output features. Workgroup tile BM (features) x BN (candidates), 2 x 2
+// waves; two workgroups share a CU, so one's prologue (index map, request
+// rows, first slabs) and epilogue run under the other's products. K arrives in
+// BK-wide slabs by LDS DMA, S - 1 slabs ahead of use; 16-byte chunks are
+// XOR-swizzled by row so that the 16 rows of a quarter-wave read fall on
+// distinct banks. Chunks past K come from a zeroed address, rows past the
+// operands repeat the last one and are not stored.
+//
+// HAS_ADD: the residual's slab travels the same way, and the sum round(x +
+// x_add) is formed on the fragments.
+//
+// Epilogue: each candidate's own request row Z[m_n] (or the bias), loaded in
+// the prologue, is added after the products (the order of the streaming
+// kernel, so the two give the same values), then the activation; the wave's
+// block goes through LDS so that a store instruction covers whole row
+// segments.
+// What bounds it: reads of the two operands through L2 (each 128 x 128 tile
+// reads 256 rows of K) and the output stores; the slab depth, the request rows
+// in the prologue or the epilogue and two to four waves a SIMD all measured
+// within 5% (the residual form gains 10% from the epilogue: 100,000 x 1024,
+// K 512: 228 / 252 us). Against register-staged slabs with one slab ahead and
+// 8-byte stores: 64,324 x 512, K 256, shuffled: 58 -> 39 us; 407,816 x 552, K
+// 104: 310 -> 241; with residual 100,000 x 1024, K 512: 265 -> 228, 20,011 x
+// 300, K 360: 27 -> 22.5.
+// ---------------------------------------------------------------------------
+__device__ __constant__ u32x4 g_zero_chunk = {0u, 0u, 0u, 0u};
+
+template <int BM, int BN, int BK, int S, bool HAS_ADD>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void ikbo_gemm_tile(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ xadd, const bf16_t* __restrict__ w,
+    const float* __restrict__ z, const int32_t* __restrict__ ids, bf16_t* __restrict__ out,
+    int64_t N, int K, int D, int tiles_m, int relu, int R) {
+  constexpr int WM = BM / 2, WN = BN / 2;      // wave block
+  constexpr int FM = WM / 32, FN = WN / 32;
+  constexpr bool ZLATE = HAS_ADD;              // request rows loaded in the epilogue
+  constexpr int ZFN = ZLATE ? 1 : FN;
+  constexpr int ROWB = 2 * BK;                 // bytes of one slab row
+  constexpr int CPR = ROWB / 16;               // its 16-byte chunks
+  constexpr int RPI = 1024 / ROWB;             // slab rows per wave-wide DMA load
+  constexpr int NA = BM / RPI / 4, NB = BN / RPI / 4;   // DMA loads per wave and slab
+  constexpr int NL = NA + (HAS_ADD ? 2 : 1) * NB;
+  constexpr int XO = BM * ROWB, AO = XO + BN * ROWB;    // candidates, residual in a stage
+  constexpr int STAGE = AO + (HAS_ADD ? BN * ROWB : 0);
+  constexpr int ORB = 2 * WM;                  // bytes of one output row of a wave's block
+  static_assert(NA >= 1 && NB >= 1 && NL * (S - 1) < 64, "staging does not tile");
+  static_assert(S * STAGE >= 4 * 32 * ORB, "the output staging reuses the ring");
+  __shared__ __attribute__((aligned(1024))) char lds[S * STAGE];
+  ROCS_LDS char* const lds3 = (ROCS_LDS char*)lds;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hh = lane >> 5;
   const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
   const int m0 = (int)(tile % (uint32_t)tiles_m) * BM;
   const int64_t n0 = (int64_t)(tile / (uint32_t)tiles_m) * BN;
-  const int wm0 = (wave % WAVES_M) * WM, wn0 = (wave / WAVES_M) * WN;
-  const int l32 = lane & 31, h4 = (lane >> 5) * 4, h8 = (lane >> 5) * 8;
+  const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
+  const uint32_t lbase = lds_addr(lds);
+  auto swz = [](int row) { return CPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; };
 
-  const int srow = tid / CPR, skc = (tid % CPR) * 8;
-  u32x4 ra[CA], rb[CB];
-  auto load_slab = [&](int k0) {
-    const bool kok = k0 + skc < K;
+  // DMA lane map: load i of this wave fills rows RPI (N? wave + i) + lane /
+  // CPR, chunk position lane % CPR, with chunk (lane % CPR) ^ swz(row).
+  const char* pa[NA];
+  const char* pb[NB];
+  int chunk_a[NA], chunk_b[NB];
 #pragma unroll
-    for (int i = 0; i < CA; ++i) {
-      const int d = m0 + srow + RPP * i;
-      ra[i] = load16(w + (int64_t)d * K + k0 + skc, kok && d < D);
-    }
+  for (int i = 0; i < NA; ++i) {
+    const int row = RPI * (NA * wave + i) + lane / CPR;
+    chunk_a[i] = 8 * ((lane % CPR) ^ swz(row));
+    pa[i] = reinterpret_cast<const char*>(w + (int64_t)min(m0 + row, D - 1) * K + chunk_a[i]);
+  }
 #pragma unroll
-    for (int i = 0; i < CB; ++i) {
-      const int64_t n = n0 + srow + RPP * i;
-      const bool ok = kok && n < N;
-      const int64_t o = n * K + k0 + skc;
-      if constexpr (HAS_ADD) {
-        // GLM pointwise residual: round(x + x_add) elementwise, in fp32.
-        const u32x4 p = load16(x + o, ok), q = load16(xadd + o, ok);
-        u32x4 s;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          s[e] = pack_bf16x2(bf16_lo(p[e]) + bf16_lo(q[e]), bf16_hi(p[e]) + bf16_hi(q[e]));
-        rb[i] = s;
-      } else {
-        rb[i] = load16(x + o, ok);
-      }
-    }
-  };
-  auto store_slab = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < CA; ++i)
-      *reinterpret_cast<u32x4*>(&lds_a[buf][srow + RPP * i][skc]) = ra[i];
-#pragma unroll
-    for (int i = 0; i < CB; ++i)
-      *reinterpret_cast<u32x4*>(&lds_b[buf][srow + RPP * i][skc]) = rb[i];
-  };
-
+  for (int i = 0; i < NB; ++i) {
+    const int row = RPI * (NB * wave + i) + lane / CPR;
+    chunk_b[i] = 8 * ((lane % CPR) ^ swz(row));
+    pb[i] = reinterpret_cast<const char*>(x + min(n0 + row, N - 1) * K + chunk_b[i]);
+  }
+  const int64_t to_add = HAS_ADD ? reinterpret_cast<const char*>(xadd) - reinterpret_cast<const char*>(x) : 0;
+  const char* const zeros = reinterpret_cast<const char*>(&g_zero_chunk);
   const int nk = (K + BK - 1) / BK;
-  load_slab(0);
-
-  // Accumulators start at b[d] + Z[m_n][d]; element 4 q + i of tile (fm, fn)
-  // is feature m0 + wm0 + 32 fm + 8 q + h4 + i of candidate n0 + wn0 + 32 fn + l32.
-  f32x16 acc[FM][FN];
-  {
-    // A request id outside [0, R) (a malformed caller map) is clamped into
-    // range: wrong rows, never an access outside Z.
-    auto req = [&](int64_t n) { return (int)min((uint32_t)ids[n], (uint32_t)(R - 1)); };
-    // Sorted ids (expanded from CSR offsets): equal first and last ids mean
-    // the whole tile has one request. A caller's map has no such order.
-    const bool one_request = z != nullptr && ids_sorted != 0 &&
-                             ids[n0] == ids[(n0 + BN < N ? n0 + BN : N) - 1];
+  auto issue = [&](int s, int slot) __attribute__((always_inline)) {
+    const uint32_t dst = lbase + (uint32_t)(slot * STAGE);
+    const int64_t at = (int64_t)s * ROWB;
+    const int left = K - s * BK;               // valid elements of the slab's rows
 #pragma unroll
-    for (int fn = 0; fn < FN; ++fn) {
-      const int64_t n = n0 + wn0 + 32 * fn + l32;
-      const float* zr = nullptr;
-      if (z != nullptr) {
-        const int r = one_request ? req(n0) : (n < N ? req(n) : 0);
-        zr = z + (int64_t)r * D;
-      }
+    for (int i = 0; i < NA; ++i)
+      lds_dma16(left >= BK || chunk_a[i] < left ? pa[i] + at : zeros,
+                dst + (uint32_t)(1024 * (NA * wave + i)));
 #pragma unroll
-      for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int d = m0 + wm0 + 32 * fm + 8 * q + h4;
-          f32x4 v = {0.f, 0.f, 0.f, 0.f};
-          if (d < D) {
-            if (bias != nullptr) v = *reinterpret_cast<const f32x4*>(bias + d);
-            if (zr != nullptr && (one_request || n < N)) v += *reinterpret_cast<const f32x4*>(zr + d);
-          }
-#pragma unroll
-          for (int i = 0; i < 4; ++i) acc[fm][fn][4 * q + i] = v[i];
-        }
+    for (int i = 0; i < NB; ++i) {
+      const bool ok = left >= BK || chunk_b[i] < left;
+      lds_dma16(ok ? pb[i] + at : zeros, dst + (uint32_t)(XO + 1024 * (NB * wave + i)));
+      if constexpr (HAS_ADD)
+        lds_dma16(ok ? pb[i] + at + to_add : zeros, dst + (uint32_t)(AO + 1024 * (NB * wave + i)));
     }
+  };
+
+  // The request row of each lane's candidates. A request id outside [0, R) (a
+  // malformed caller map) is clamped into range: wrong rows, never an access
+  // outside Z.
+  int rq[FN];
+#pragma unroll
+  for (int fn = 0; fn < FN; ++fn) {
+    const int64_t n = min(n0 + wn0 + 32 * fn + l32, N - 1);
+    rq[fn] = ids != nullptr ? (int)min((uint32_t)ids[n], (uint32_t)(R - 1)) : 0;
+  }
+#pragma unroll
+  for (int s = 0; s < S - 1; ++s)
+    if (s < nk) issue(s, s);
+  f32x4 zv[ZFN][FM][4];
+  auto load_z = [&](int fn) __attribute__((always_inline)) {
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int d = m0 + wm0 + 32 * fm + 8 * q + 4 * hh;
+        zv[fn % ZFN][fm][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (z != nullptr && d < D)
+          zv[fn % ZFN][fm][q] = *reinterpret_cast<const f32x4*>(z + (int64_t)rq[fn] * D + d);
+      }
+  };
+  if constexpr (!ZLATE) {
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn) load_z(fn);
   }
 
-  store_slab(0);
-  __syncthreads();
+  // Fragments: row 32 f + l32 of the wave's block, chunk 2 ks + hh; the
+  // swizzle turns the k-step into an XOR with 32 ks.
+  const uint32_t fr = (uint32_t)(l32 * ROWB + 16 * (hh ^ swz(l32)));
+  const uint32_t fa = (uint32_t)(wm0 * ROWB) + fr, fb = (uint32_t)(XO + wn0 * ROWB) + fr;
+  f32x16 acc[FM][FN];
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = f32x16{};
+  int slot = 0, next = S - 1;
   for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) load_slab((kt + 1) * BK);
+    // Slab kt resident: everything but the S - 2 slabs issued after it.
+    if (kt + S - 2 < nk) wait_vmcnt<(S - 2) * NL>(); else wait_vmcnt<0>();
+    ring_barrier();                            // ... of every wave; slab kt - 1's slot is free
+    if (kt + S - 1 < nk) issue(kt + S - 1, next);
+    const uint32_t so = (uint32_t)(slot * STAGE);
 #pragma unroll
     for (int ks = 0; ks < BK / 16; ++ks) {
       bf16x8 af[FM], bfr[FN];
 #pragma unroll
       for (int fm = 0; fm < FM; ++fm)
-        af[fm] = *reinterpret_cast<const bf16x8*>(&lds_a[cur][wm0 + 32 * fm + l32][ks * 16 + h8]);
+        af[fm] = *reinterpret_cast<const ROCS_LDS bf16x8*>(
+            lds3 + so + 32 * fm * ROWB + (fa ^ (32u * ks)));
 #pragma unroll
-      for (int fn = 0; fn < FN; ++fn)
-        bfr[fn] = *reinterpret_cast<const bf16x8*>(&lds_b[cur][wn0 + 32 * fn + l32][ks * 16 + h8]);
+      for (int fn = 0; fn < FN; ++fn) {
+        bfr[fn] = *reinterpret_cast<const ROCS_LDS bf16x8*>(
+            lds3 + so + 32 * fn * ROWB + (fb ^ (32u * ks)));
+        if constexpr (HAS_ADD) {
+          const u32x4 p = as_u32x4(bfr[fn]);
+          const u32x4 q = *reinterpret_cast<const ROCS_LDS u32x4*>(
+              lds3 + so + (AO - XO) + 32 * fn * ROWB + (fb ^ (32u * ks)));
+          u32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            v[e] = pack_bf16x2(bf16_lo(p[e]) + bf16_lo(q[e]), bf16_hi(p[e]) + bf16_hi(q[e]));
+          bfr[fn] = as_bf16x8(v);
+        }
+      }
 #pragma unroll
       for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
         for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = mfma32(af[fm], bfr[fn], acc[fm][fn]);
     }
-    if (kt + 1 < nk) store_slab(cur ^ 1);
-    __syncthreads();
+    slot = slot + 1 == S ? 0 : slot + 1;
+    next = next + 1 == S ? 0 : next + 1;
   }
+  ring_barrier();                              // the ring is free
 
-  // Epilogue: activation, round to bf16, 8-byte stores.
+  // Element 4 q + i of acc[fm][fn] is feature 32 fm + 8 q + 4 hh + i of
+  // candidate 32 fn + l32. After the half-wave swap lane (l32, hh) holds
+  // features 32 fm + 16 j + 8 hh .. + 7: one 16-byte chunk of its row in the
+  // wave's staging area, at chunk position ^ row.
+  const uint32_t st = (uint32_t)(wave * 32 * ORB);
+  const int64_t nw = n0 + wn0;
+  const int dw = m0 + wm0;
 #pragma unroll
   for (int fn = 0; fn < FN; ++fn) {
-    const int64_t n = n0 + wn0 + 32 * fn + l32;
-    if (n >= N) continue;
+    if constexpr (ZLATE) load_z(fn);
 #pragma unroll
     for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int d = m0 + wm0 + 32 * fm + 8 * q + h4;
-        if (d >= D) continue;
-        float v[4];
+      for (int j = 0; j < 2; ++j) {
+        uint32_t p[2][2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = relu ? fmaxf(acc[fm][fn][4 * q + i], 0.f) : acc[fm][fn][4 * q + i];
-        *reinterpret_cast<u32x2*>(out + n * D + d) =
-            u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+        for (int u = 0; u < 2; ++u) {
+          const f32x16& a = acc[fm][fn];
+          const f32x4 zq = zv[fn % ZFN][fm][2 * j + u];
+          const int e = 4 * (2 * j + u);
+          p[u][0] = pack_bf16x2(a[e] + zq[0], a[e + 1] + zq[1]);
+          p[u][1] = pack_bf16x2(a[e + 2] + zq[2], a[e + 3] + zq[3]);
+          if (relu) {
+            p[u][0] = relu_bf16x2(p[u][0]);
+            p[u][1] = relu_bf16x2(p[u][1]);
+          }
+        }
+        const auto s0 = __builtin_amdgcn_permlane32_swap(p[0][0], p[1][0], false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(p[0][1], p[1][1], false, false);
+        const int ch = (4 * fm + 2 * j + hh) ^ (l32 & (ORB / 16 - 1));
+        *reinterpret_cast<ROCS_LDS u32x4*>(lds3 + st + l32 * ORB + 16 * ch) =
+            u32x4{s0[0], s1[0], s0[1], s1[1]};
       }
+    // Read back row-contiguous; 16-byte stores where the rows allow them.
+    if (D % 8 == 0) {
+      constexpr int LPR = ORB / 16;            // lanes per row
+#pragma unroll
+      for (int i = 0; i < 32 * LPR / 64; ++i) {
+        const int r = (64 / LPR) * i + lane / LPR, c = lane % LPR;
+        const u32x4 v = *reinterpret_cast<const ROCS_LDS u32x4*>(
+            lds3 + st + r * ORB + 16 * (c ^ (r & (ORB / 16 - 1))));
+        const int64_t n = nw + 32 * fn + r;
+        const int d = dw + 8 * c;
+        if (n < N && d < D) *reinterpret_cast<u32x4*>(out + n * D + d) = v;
+      }
+    } else {
+      constexpr int LPR = ORB / 8;
+#pragma unroll
+      for (int i = 0; i < 32 * LPR / 64; ++i) {
+        const int r = (64 / LPR) * i + lane / LPR, c = lane % LPR;
+        const u32x2 v = *reinterpret_cast<const ROCS_LDS u32x2*>(
+            lds3 + st + r * ORB + 16 * ((c >> 1) ^ (r & (ORB / 16 - 1))) + 8 * (c & 1));
+        const int64_t n = nw + 32 * fn + r;
+        const int d = dw + 4 * c;
+        if (n < N && d < D) *reinterpret_cast<u32x2*>(out + n * D + d) = v;
+      }
+    }
   }
 }
 
@@ -332,17 +423,6 @@ void ikbo_gemm_bf16(
 // ---------------------------------------------------------------------------
 constexpr int kStreamBM = 256, kStreamBN = 256, kStreamBK = 64;
 constexpr int kCpolNT = 2;   // buffer-instruction cache policy bits: NT (the former SLC bit)
-
-// ReLU of two packed bf16 values: as 16-bit integers the negative values
-// (sign bit set) are exactly those below zero, so a packed integer max with
-// zero clamps them (and -0) to +0. Written as the one instruction: the
-// compiler's own lowering of a packed max on a bit-cast pair has been seen
-// to drop the second word of the pair.
-__device__ __forceinline__ uint32_t relu_bf16x2(uint32_t p) {
-  uint32_t r;
-  asm("v_pk_max_i16 %0, %1, 0" : "=v"(r) : "v"(p));
-  return r;
-}
 
 struct StreamTile {
   int slot;       // tile slot (candidate block)
@@ -966,26 +1046,17 @@ hipError_t launch_general(GeneralArgs<T> g, hipStream_t s) {
   return vec ? go(linear_general<T, 32, true, OUTF, EXT>) : go(linear_general<T, 32, false, OUTF, EXT>);
 }
 
-template <int BM, int BN, int BK, int WMW, int WNW>
-hipError_t launch_fast_gemm(const LinearArgs& a, hipStream_t s) {
+template <int BM, int BN, int BK, int S, bool HAS_ADD>
+hipError_t launch_tile(const LinearArgs& a, hipStream_t s) {
   const int tiles_m = (int)((a.d_out + BM - 1) / BM);
-  const int64_t tiles_n = (a.N + BN - 1) / BN;
-  const int64_t grid = tiles_m * tiles_n;
-  if (!grid_fits(grid, 64 * WMW * WNW)) return hipErrorInvalidConfiguration;
-  const bf16_t* x = static_cast<const bf16_t*>(a.x_cand);
-  const bf16_t* xa = static_cast<const bf16_t*>(a.x_cand_add);
-  const bf16_t* w = static_cast<const bf16_t*>(a.w_cand);
-  bf16_t* o = static_cast<bf16_t*>(a.out);
-  const float* z = a.k_req > 0 ? a.z : nullptr;
-  if (xa != nullptr)
-    return launch_kernel(ikbo_gemm_bf16<BM, BN, BK, WMW, WNW, true>, dim3((uint32_t)grid),
-                         dim3(64 * WMW * WNW), s,
-                         x, xa, w, a.bias, z, a.ids, o, a.N, (int)a.k_cand, (int)a.d_out,
-                         tiles_m, (int)a.relu, (int)a.R, (int)!a.ids_given);
-  return launch_kernel(ikbo_gemm_bf16<BM, BN, BK, WMW, WNW, false>, dim3((uint32_t)grid),
-                       dim3(64 * WMW * WNW), s,
-                       x, xa, w, a.bias, z, a.ids, o, a.N, (int)a.k_cand, (int)a.d_out,
-                       tiles_m, (int)a.relu, (int)a.R, (int)!a.ids_given);
+  const int64_t grid = tiles_m * ((a.N + BN - 1) / BN);
+  if (!grid_fits(grid, 256)) return hipErrorInvalidConfiguration;
+  return launch_kernel(ikbo_gemm_tile<BM, BN, BK, S, HAS_ADD>, dim3((uint32_t)grid), dim3(256), s,
+                       static_cast<const bf16_t*>(a.x_cand),
+                       static_cast<const bf16_t*>(a.x_cand_add),
+                       static_cast<const bf16_t*>(a.w_cand), a.k_req > 0 ? a.z : a.bias,
+                       a.k_req > 0 ? a.ids : nullptr, static_cast<bf16_t*>(a.out), a.N,
+                       (int)a.k_cand, (int)a.d_out, tiles_m, (int)a.relu, (int)a.R);
 }
 
 template <typename T>
@@ -1063,16 +1134,29 @@ hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
   // caller's per-candidate map takes the kernel with per-row request lookup.
   // (K and D bounds: the kernel's per-lane load and store offsets within a
   // 256-row tile are 32-bit.)
-  const bool stream = !a.ids_given && a.x_cand_add == nullptr && a.k_cand % kStreamBK == 0 &&
+  int cus = 0;
+  const hipError_t ce = current_cu_count(&cus);
+  if (ce != hipSuccess) return ce;
+  const int64_t tiles_m256 = (a.d_out + kStreamBM - 1) / kStreamBM;
+  const int64_t slots = (a.k_req > 0 ? a.R : 0) + (a.N + kStreamBN - 1) / kStreamBN;
+  const bool can_stream = !a.ids_given && a.x_cand_add == nullptr && a.k_cand % kStreamBK == 0 &&
                       a.k_cand < (int64_t(1) << 22) && a.d_out < (int64_t(1) << 22) &&
-                      ((a.k_req > 0 ? a.R : 0) + (a.N + kStreamBN - 1) / kStreamBN) *
-                              ((a.d_out + kStreamBM - 1) / kStreamBM) < (int64_t(1) << 31);
+                      slots * tiles_m256 < (int64_t(1) << 31);
   // On request, the streaming kernel also runs the request side (combined
   // kernel); otherwise the request GEMM is a launch of its own. Separate
   // launches are the default on this part: the cross-XCD release / acquire
   // the combined kernel needs (an L2 write-back per request tile, an L2
   // invalidate per workgroup) costs more than the launch it saves.
-  const bool fused = a.combined && stream && a.k_req > 0 && a.N > 0;
+  const bool fused = a.combined && can_stream && a.k_req > 0 && a.N > 0;
+  // The streaming kernel's workgroups, one per CU, take whole 256 x 256 tiles,
+  // so its time is that of its last round; the tiled kernel's smaller tiles
+  // pack better but stream K at about 0.7 of its rate. Measured (us, streaming
+  // / tiled, with the share of the rounds' area that the call fills): 0.25,
+  // 8,192 x 512, K 2048: 54 / 37; 0.51, 50,000 x 512: 60 / 48; 0.65, 64,324 x
+  // 512: 45 / 35; 0.73, 48,000 x 512: 37 / 38; 0.75, 24,576 x 512: 18 / 21;
+  // 0.76, 100,000 x 1024: 135 / 172; 1, 163,840 x 1024: 107 / 158.
+  const int64_t rounds = (slots * tiles_m256 + cus - 1) / cus;
+  const bool stream = can_stream && (fused || 4 * a.N * a.d_out >= 3 * rounds * cus * kStreamBM * kStreamBN);
   RequestOut yr{static_cast<const bf16_t*>(a.w_rr), a.b_rr, static_cast<bf16_t*>(a.y_req),
                 (int)a.d_req, a.y_req != nullptr ? (int)((a.d_req + 15) / 16) : 0, (int)a.relu};
   // No candidates: only the Y^R tiles (the request table has no reader).
@@ -1093,12 +1177,8 @@ hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
   }
   if (a.N == 0) return hipSuccess;      // request-side output only
   if (stream) {
-    const int tiles_m = (int)((a.d_out + kStreamBM - 1) / kStreamBM);
-    const int64_t slots = (a.k_req > 0 ? a.R : 0) + (a.N + kStreamBN - 1) / kStreamBN;
+    const int tiles_m = (int)tiles_m256;
     const int64_t n_tiles = slots * tiles_m;
-    int cus = 0;
-    const hipError_t e = current_cu_count(&cus);
-    if (e != hipSuccess) return e;
     const int grid = (int)(n_tiles < cus ? n_tiles : cus);
     const StreamStep step{grid / tiles_m, grid % tiles_m};
     const float* zb = a.k_req > 0 ? a.z : a.bias;
@@ -1130,13 +1210,13 @@ hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
       return a.relu ? go(ikbo_gemm_stream<true, true, false>) : go(ikbo_gemm_stream<true, false, false>);
     return a.relu ? go(ikbo_gemm_stream<false, true, false>) : go(ikbo_gemm_stream<false, false, false>);
   }
-  // Large tiles when they still give every CU at least four tiles. The bias
-  // is already inside Z when there is a request term.
-  LinearArgs b = a;
-  if (a.k_req > 0) b.bias = nullptr;
-  const int64_t big_tiles = ((a.d_out + 255) / 256) * ((a.N + 127) / 128);
-  if (big_tiles >= 1024) return launch_fast_gemm<256, 128, 32, 2, 2>(b, s);
-  return launch_fast_gemm<128, 128, 32, 2, 2>(b, s);
+  // 64 x 64 tiles while 128 x 128 ones would leave CUs without a workgroup
+  // (613 x 1024, K 256: 3.7 against 6.0 us; 2,000 x 1024, K 512: 10.3 / 12.9;
+  // 8,192 x 512, K 2048, 256 tiles: 41.5 / 37.8).
+  const bool small = ((a.d_out + 127) / 128) * ((a.N + 127) / 128) < cus;
+  if (a.x_cand_add != nullptr)
+    return small ? launch_tile<64, 64, 64, 3, true>(a, s) : launch_tile<128, 128, 32, 2, true>(a, s);
+  return small ? launch_tile<64, 64, 64, 3, false>(a, s) : launch_tile<128, 128, 32, 3, false>(a, s);
 }
 
 }  // namespace rocs
