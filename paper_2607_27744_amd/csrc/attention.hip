@@ -626,6 +626,263 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(D == 64 
 }
 
 // ---------------------------------------------------------------------------
+// The same attention for calls of few tiles (bf16, head_dim 64 or 128): a
+// workgroup takes 32 query rows of one head and its four waves split the
+// history, wave w taking stages w, w + 4, ... of 64 keys. With 128-row tiles
+// such a call leaves most CUs idle, and each workgroup walks the whole history
+// alone; here there are four times the workgroups, each a quarter of the walk.
+// Every wave stages K and V in LDS of its own (DMA, the next K under the
+// softmax, the next V under the next scores), so the waves meet only to merge
+// their partial softmaxes at the end. The layouts, the weights rounded to bf16
+// and the row sums taken from them are those of the tiled kernel; the running
+// max moves at every stage.
+// What bounds it: the latency of a wave's chain of stages. At one request of
+// 203 candidates, history 613, 4 heads x 64 it takes 6.4 us (128-row tiles:
+// 11.7 us), at 16 requests of 32 query rows, history 1024: 7.7 us (15.4 us).
+// ---------------------------------------------------------------------------
+constexpr int kSplitRows = 32;
+
+template <int D, bool MAPPED, bool QPROJ>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void dca_attn_split(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
+    const int32_t* __restrict__ cand_off, const int32_t* __restrict__ kv_off,
+    bf16_t* __restrict__ out, int R, int Tq, int H, int64_t kv_stride, float scale_log2,
+    int slots_per_head, const int32_t* __restrict__ order, const bf16_t* __restrict__ res,
+    bf16_t* __restrict__ out_sum, const bf16_t* __restrict__ wq) {
+  constexpr int W = 4, TR = kSplitRows;
+  constexpr int KB = kTileKeys / 32, KS = D / 16, DB = D / 32, PS = kTileKeys / 16;
+  constexpr int ROWB = 2 * D, CR = D / 8;
+  constexpr int STAGE = kTileKeys * ROWB;             // bytes of one K (or V) stage
+  constexpr int KPI = 1024 / ROWB;                    // rows per wave-wide DMA load
+  constexpr int NI = kTileKeys / KPI;                 // DMA loads per stage and operand
+  constexpr int OP = D + 4;                           // floats of one partial output row
+  static_assert(TR * OP * 4 <= 2 * STAGE, "a wave's partial output takes its staging");
+  __shared__ __attribute__((aligned(1024))) char lds[W * 2 * STAGE];
+  __shared__ float pm[W][TR], pl[W][TR];
+  ROCS_LDS char* const lds3 = (ROCS_LDS char*)lds;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hh = lane >> 5;
+  const uint32_t work = xcd_remap(blockIdx.x, gridDim.x);
+  const int h = __builtin_amdgcn_readfirstlane((int)(work / (uint32_t)slots_per_head));
+  const int64_t slot = work - (uint32_t)h * (uint32_t)slots_per_head;
+  const int r = request_of_slot(cand_off, R, slot, Tq, TR);
+  const int64_t rend = (int64_t)cand_off[r + 1] * Tq;
+  const int64_t row0 = (int64_t)cand_off[r] * Tq + (slot - tile_base(cand_off, r, Tq, TR)) * TR;
+  if (row0 >= rend) return;                               // idle slot
+  const int rows = (int)(rend - row0 < TR ? rend - row0 : TR);
+  const int64_t kv0 = kv_off[r];
+  const int L = kv_off[r + 1] - (int)kv0;
+  const int64_t qs = (int64_t)H * D;
+  auto src_row = [&](int i) -> int64_t {
+    const int64_t gr = row0 + i;
+    if constexpr (MAPPED) {
+      const int64_t p = gr / Tq;
+      return (int64_t)order[p] * Tq + (gr - p * Tq);
+    } else {
+      return gr;
+    }
+  };
+  // DMA lane map of a stage: load i fills rows KPI i + lane / CR, chunk
+  // position lane % CR, with chunk (lane % CR) ^ kv_swizzle(row).
+  const char* kbase = reinterpret_cast<const char*>(k + kv0 * kv_stride + (int64_t)h * D);
+  const char* vbase = reinterpret_cast<const char*>(v + kv0 * kv_stride + (int64_t)h * D);
+  const int64_t rowstride = kv_stride * 2;
+  const uint32_t kdst = lds_addr(lds) + (uint32_t)(wave * 2 * STAGE);
+  auto issue = [&](const char* src, int t, uint32_t dst) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int row = KPI * i + lane / CR;
+      lds_dma16(src + (int64_t)min(t * kTileKeys + row, L - 1) * rowstride +
+                    16 * ((lane % CR) ^ kv_swizzle<D>(row)),
+                dst + 1024u * i);
+    }
+  };
+  // Query rows as B fragments, all waves the same 32 (projected as in the
+  // tiled kernel, W_q,h staged in the K/V area first).
+  const int qrow = min(l32, rows - 1);                    // clamped; extra rows never stored
+  const int ntiles = (L + kTileKeys - 1) / kTileKeys;
+  bf16x8 qf[KS];
+  if constexpr (!QPROJ) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      qf[ks] = *reinterpret_cast<const bf16x8*>(q + (int64_t)h * D + src_row(qrow) * qs + 16 * ks + 8 * hh);
+  } else {
+    constexpr int PK = kProjIn / 16, PRB = kProjIn * 2, PNI = D * PRB / 1024 / W;
+    static_assert(D == 64 && W * 2 * STAGE >= D * PRB, "projection staging");
+    const char* wsrc = uniform_ptr(reinterpret_cast<const char*>(wq + (int64_t)h * D * kProjIn));
+    const uint32_t lb = lds_addr(lds);
+#pragma unroll
+    for (int i = 0; i < PNI; ++i) {
+      const int blk = wave * PNI + i;                     // 1 KiB: rows 2 blk, 2 blk + 1
+      const int prow = 2 * blk + (lane >> 5), pos = lane & 31;
+      lds_dma16_sv(wsrc, (uint32_t)(prow * PRB + 16 * (pos ^ (prow & 15))), lb + 1024u * blk);
+    }
+    const bf16_t* xr = q + src_row(qrow) * kProjIn + 8 * hh;
+    bf16x8 xq[PK];
+#pragma unroll
+    for (int s2 = 0; s2 < PK; ++s2) xq[s2] = *reinterpret_cast<const bf16x8*>(xr + 16 * s2);
+    wait_vmcnt<0>();
+    ring_barrier();
+    f32x16 pacc[2] = {};
+#pragma unroll
+    for (int s2 = 0; s2 < PK; ++s2)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int prow = 32 * b + l32;
+        const bf16x8 a = *reinterpret_cast<const ROCS_LDS bf16x8*>(
+            lds3 + prow * PRB + 16 * ((2 * s2 + hh) ^ (prow & 15)));
+        pacc[b] = mfma32(a, xq[s2], pacc[b]);
+      }
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) {
+        const f32x16& pa = pacc[b];
+        const uint32_t e0 = pack_bf16x2(pa[8 * jj], pa[8 * jj + 1]);
+        const uint32_t e1 = pack_bf16x2(pa[8 * jj + 2], pa[8 * jj + 3]);
+        const uint32_t o0 = pack_bf16x2(pa[8 * jj + 4], pa[8 * jj + 5]);
+        const uint32_t o1 = pack_bf16x2(pa[8 * jj + 6], pa[8 * jj + 7]);
+        const auto t0 = __builtin_amdgcn_permlane32_swap(e0, o0, false, false);
+        const auto t1 = __builtin_amdgcn_permlane32_swap(e1, o1, false, false);
+        qf[2 * b + jj] = as_bf16x8(u32x4{t0[0], t1[0], t0[1], t1[1]});
+      }
+    wait_lgkmcnt0();
+    ring_barrier();                                       // W_q's LDS goes to K and V
+  }
+  // The query rows resident before the first DMA load: the stage loop then
+  // has only DMA loads in flight, which the waits below count.
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) asm volatile("" :: "v"(as_u32x4(qf[ks])));
+
+  const uint32_t kb0 = (uint32_t)(wave * 2 * STAGE);
+  const uint32_t ka0 = kb0 + (uint32_t)(l32 * ROWB + 16 * (hh ^ kv_swizzle<D>(l32)));
+  uint32_t va0[2];
+#pragma unroll
+  for (int rr = 0; rr < 2; ++rr) {
+    const int g = lane >> 4, jl = lane & 15;
+    const int key = 4 * (g >> 1) + 8 * rr + (jl >> 2);
+    const int chunk0 = 2 * (g & 1) + ((jl & 3) >> 1);
+    va0[rr] = kb0 + (uint32_t)(STAGE + key * ROWB + 16 * (chunk0 ^ kv_swizzle<D>(key)) + 8 * (jl & 1));
+  }
+  float m = -INFINITY, l_part = 0.f;
+  f32x16 oacc[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) oacc[db] = f32x16{};
+  if (wave < ntiles) {
+    issue(kbase, wave, kdst);
+    issue(vbase, wave, kdst + STAGE);
+  }
+  for (int t = wave; t < ntiles; t += W) {
+    const bool more = t + W < ntiles;
+    wait_vmcnt<NI>();                                     // K of t (V of t may be in flight)
+    asm volatile("" ::: "memory");
+    f32x16 sacc[KB] = {};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+        const bf16x8 a = *reinterpret_cast<const ROCS_LDS bf16x8*>(
+            lds3 + ((ka0 ^ (32u * ks)) + kb * 32 * ROWB));
+        sacc[kb] = mfma32(a, qf[ks], sacc[kb]);
+      }
+    wait_lgkmcnt0();                                      // K's fragments are in registers
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    if (more) issue(kbase, t + W, kdst);
+    if (t == ntiles - 1) {                                // keys past the history's end
+      const int valid = L - t * kTileKeys;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (32 * kb + 8 * (e / 4) + 4 * hh + e % 4 >= valid) sacc[kb][e] = -INFINITY;
+    }
+    float mx = sacc[0][0];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[kb][e]);
+    const float mn = fmaxf(m, max_across_halves(mx) * scale_log2);
+    const float ms = mn == -INFINITY ? 0.f : mn;          // no finite score yet: weights 0
+    const float alpha = exp2f(m - ms);
+    m = mn;
+    l_part *= alpha;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) oacc[db] *= alpha;
+    // Each packed pair is a scalar of its own (see exp_block above).
+    uint32_t pk[PS][4];
+    const bf16x2 ones = {(bf16_t)1.0f, (bf16_t)1.0f};
+#pragma unroll
+    for (int ps = 0; ps < PS; ++ps)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float s0 = sacc[ps / 2][8 * (ps % 2) + 2 * w];
+        const float s1 = sacc[ps / 2][8 * (ps % 2) + 2 * w + 1];
+        pk[ps][w] = pack_bf16x2(__builtin_amdgcn_exp2f(fmaf(s0, scale_log2, -ms)),
+                                __builtin_amdgcn_exp2f(fmaf(s1, scale_log2, -ms)));
+        l_part = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[ps][w]), ones,
+                                                 l_part, false);
+      }
+    if (more) wait_vmcnt<NI>(); else wait_vmcnt<0>();     // V of t (K of t + 4 in flight)
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int ps = 0; ps < PS; ++ps) {
+      const bf16x8 pf = as_bf16x8(u32x4{pk[ps][0], pk[ps][1], pk[ps][2], pk[ps][3]});
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        const uint32_t off = ps * 16 * ROWB;
+        const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (ROCS_LDS i16x4*)(lds3 + ((va0[0] ^ (64u * db)) + off))));
+        const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (ROCS_LDS i16x4*)(lds3 + ((va0[1] ^ (64u * db)) + off))));
+        oacc[db] = mfma32(as_bf16x8(u32x4{lo[0], lo[1], hi[0], hi[1]}), pf, oacc[db]);
+      }
+    }
+    wait_lgkmcnt0();                                      // V's fragments are in registers
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    if (more) issue(vbase, t + W, kdst + STAGE);
+  }
+  // This wave's partial softmax into its staging area: element 4 qq + i of
+  // oacc[db] is O[row l32][dim 32 db + 8 qq + 4 hh + i].
+  const float l_sum = sum_across_halves(l_part);
+  if (hh == 0) {
+    pm[wave][l32] = m;
+    pl[wave][l32] = l_sum;
+  }
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int qq = 0; qq < 4; ++qq)
+      *reinterpret_cast<ROCS_LDS f32x4*>(lds3 + kb0 + 4 * (l32 * OP + 32 * db + 8 * qq + 4 * hh)) =
+          f32x4{oacc[db][4 * qq], oacc[db][4 * qq + 1], oacc[db][4 * qq + 2], oacc[db][4 * qq + 3]};
+  __syncthreads();
+  for (int c = tid; c < rows * CR; c += 256) {            // one 16-byte piece of an output row
+    const int i = c / CR, d0 = 8 * (c % CR);
+    const float mx = fmaxf(fmaxf(pm[0][i], pm[1][i]), fmaxf(pm[2][i], pm[3][i]));
+    const float ms = mx == -INFINITY ? 0.f : mx;
+    float l = 0.f;
+    f32x4 y0 = {0.f, 0.f, 0.f, 0.f}, y1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const float f = exp2f(pm[w][i] - ms);
+      const ROCS_LDS char* src = lds3 + w * 2 * STAGE + 4 * (i * OP + d0);
+      l += pl[w][i] * f;
+      y0 += *reinterpret_cast<const ROCS_LDS f32x4*>(src) * f;
+      y1 += *reinterpret_cast<const ROCS_LDS f32x4*>(src + 16) * f;
+    }
+    const float inv = L > 0 ? 1.0f / l : 0.f;             // empty history: zeros
+    const u32x4 y = {pack_bf16x2(y0[0] * inv, y0[1] * inv), pack_bf16x2(y0[2] * inv, y0[3] * inv),
+                     pack_bf16x2(y1[0] * inv, y1[1] * inv), pack_bf16x2(y1[2] * inv, y1[3] * inv)};
+    const int64_t o = src_row(i) * qs + (int64_t)h * D + d0;
+    *reinterpret_cast<u32x4*>(out + o) = y;
+    if (res != nullptr)
+      *reinterpret_cast<u32x4*>(out_sum + o) = add_bf16x8(y, *reinterpret_cast<const u32x4*>(res + o));
+  }
+}
+
+// ---------------------------------------------------------------------------
 // General kernel: any dtype, head_dim <= 256, any stride.
 //
 // A workgroup takes 16 consecutive query rows of one head; its four waves
@@ -1110,6 +1367,28 @@ hipError_t launch_fast(const AttentionArgs& a, const int32_t* cand_off, const in
                        hipStream_t s) {
   constexpr int W = attn_waves<D>(), TR = 32 * W;
   const int64_t slots = a.R + (a.N * a.q_len + TR - 1) / TR;
+  // Few rows: 32-row tiles with the history split over the waves, while those
+  // tiles fit the CUs at once (two workgroups a CU at head_dim 64, one at 128)
+  // and the requests alone would not fill them (then 128-row tiles stream the
+  // histories better). Measured (us, 128-row / split): one request of 203,
+  // history 613, 4 x 64: 11.7 / 6.4; 16 x 200, 600, 4 x 64 (400 tiles of 32
+  // rows): 12.4 / 9.5; 32 x 200 (800): 16.5 / 16.7; 1000, 2048, 8 x 128 (250):
+  // 36.8 / 24.9; 64 rows x 4, 1000, 8 x 128 (512): 21.5 / 26.0; 100 requests
+  // of 32 rows, 500, 4 x 64: 12.8 / 15.4.
+  int cus = 0;
+  const hipError_t ce = current_cu_count(&cus);
+  if (ce != hipSuccess) return ce;
+  if (a.N * a.q_len * a.heads <= (int64_t)kSplitRows * cus * (D == 64 ? 2 : 1) &&
+      a.R * a.heads <= cus) {
+    const int64_t slots32 = a.R + (a.N * a.q_len + kSplitRows - 1) / kSplitRows;
+    return launch_kernel(dca_attn_split<D, MAPPED, QPROJ>, dim3((uint32_t)(slots32 * a.heads)),
+                         dim3(256), s, static_cast<const bf16_t*>(a.q),
+                         static_cast<const bf16_t*>(a.k), static_cast<const bf16_t*>(a.v), cand_off,
+                         a.kv_offsets, static_cast<bf16_t*>(a.out), (int)a.R, a.q_len, a.heads,
+                         a.kv_stride, a.scale * 1.4426950408889634f, (int)slots32, order,
+                         static_cast<const bf16_t*>(a.residual), static_cast<bf16_t*>(a.out_sum),
+                         static_cast<const bf16_t*>(a.proj_w));
+  }
   constexpr int64_t kRound = (int64_t)kNumXcd * kPlanChunk;
   const int32_t* plan = MAPPED ? nullptr : a.plan;
   const int64_t grid = plan != nullptr ? (slots * a.heads + kRound - 1) / kRound * kRound

@@ -191,6 +191,14 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const ROCS_LDS void*)p);
 }
 
+// A wave-uniform pointer, in scalar registers for certain.
+__device__ __forceinline__ const char* uniform_ptr(const char* p) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+  return reinterpret_cast<const char*>((uint64_t)hi << 32 | lo);
+}
+
 // 16 bytes per lane from global memory straight into LDS (the DMA form of
 // global_load_dwordx4): lane i's bytes land at dst + 16 i, dst wave-uniform.
 // Written as inline assembly on purpose: the compiler does not see an LDS

@@ -429,3 +429,42 @@ def test_mapped_grouping_edges(gpu_lib, n, r):
     np.testing.assert_array_equal(order, np.argsort(m, kind="stable"))
     np.testing.assert_array_equal(raw[:r + 1], np.concatenate([[0], np.cumsum(np.bincount(m, minlength=r))]))
     np.testing.assert_array_equal(got[:, 0, 0, 0], host(v)[m, 0, 0])
+
+
+# The split-history kernel (few 32-row tiles): its four waves with no, one and
+# several stages, ragged last stages, rows at the tile's edge, empty histories,
+# scores that move the running max between waves, and an infinite score; then
+# the same rows on the tiled kernel (more rows than the split form takes).
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("q_len", [1, 3])
+@pytest.mark.parametrize("scale", [None, 4.0])
+def test_split_history(gpu_lib, head_dim, q_len, scale):
+    counts, lens = [1, 31, 0, 32, 33, 7, 5, 2], [1, 64, 50, 65, 256, 0, 257, 1030]
+    case = wl.attention_case(counts, lens, 2, head_dim, q_len=q_len, seed=head_dim + q_len)
+    got, want = _attn(case, scale), _want(case, scale)
+    assert_close(got, want, f"split d{head_dim} T{q_len} scale {scale}")
+    n = case.q.shape[0]
+    more = -(-70000 // (n * q_len))                      # the same requests, many times over
+    big = ops.dca_attention(
+        dev_bf16(np.concatenate([case.q] * more)), dev_bf16(np.concatenate([case.k] * more)),
+        dev_bf16(np.concatenate([case.v] * more)), dev_i32(wl.offsets_from_counts(counts * more)),
+        dev_i32(wl.offsets_from_counts(lens * more)), scale=scale)
+    assert_close(host(big)[:n], got, "tiled kernel", atol=8e-3, rtol=1.6e-2)   # 2 bf16 ulps
+
+
+def test_split_history_infinite_scores(gpu_lib):
+    # A key whose score is -inf takes no part, in whichever wave it falls;
+    # NaN stays in its row.
+    case = wl.attention_case([40], [300], 1, 64, seed=3)
+    k = case.k.copy()
+    q = np.abs(case.q)
+    k[[5, 70, 130, 200, 299]] = -np.inf
+    q[7] = np.nan
+    got = host(ops.dca_attention(dev_bf16(q), dev_bf16(k), dev_bf16(case.v),
+                                 dev_i32(case.cand_offsets), dev_i32(case.kv_offsets)))
+    keep = np.isfinite(k[:, 0, 0])
+    want = ikbo.dca_attention(q, case.k[keep], case.v[keep], case.cand_offsets, np.array([0, 295]),
+                              mode="explicit")
+    rows = np.arange(40) != 7
+    assert_close(got[rows], round_bf16(want)[rows], "masked keys")
+    assert np.all(np.isnan(got[7]))
