@@ -1150,13 +1150,16 @@ hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
   const bool fused = a.combined && can_stream && a.k_req > 0 && a.N > 0;
   // The streaming kernel's workgroups, one per CU, take whole 256 x 256 tiles,
   // so its time is that of its last round; the tiled kernel's smaller tiles
-  // pack better but stream K at about 0.7 of its rate. Measured (us, streaming
-  // / tiled, with the share of the rounds' area that the call fills): 0.25,
-  // 8,192 x 512, K 2048: 54 / 37; 0.51, 50,000 x 512: 60 / 48; 0.65, 64,324 x
-  // 512: 45 / 35; 0.73, 48,000 x 512: 37 / 38; 0.75, 24,576 x 512: 18 / 21;
-  // 0.76, 100,000 x 1024: 135 / 172; 1, 163,840 x 1024: 107 / 158.
-  const int64_t rounds = (slots * tiles_m256 + cus - 1) / cus;
-  const bool stream = can_stream && (fused || 4 * a.N * a.d_out >= 3 * rounds * cus * kStreamBM * kStreamBN);
+  // pack better but stream K more slowly, the more so the longer K is.
+  // Measured (us, streaming / tiled, with the share of the rounds' area that
+  // the call fills): K 256: 0.65, 64,324 x 512: 45 / 35; 0.76, 100,000 x 512:
+  // 50 / 51, 200,000 x 256: 60 / 53; 1, 163,840 x 1024: 107 / 158. K 512 and
+  // more: 0.25, 8,192 x 512: 54 / 37; 0.51, 50,000 x 512: 60 / 48; 0.67, 8,192
+  // x 8,192: 92 / 117; 0.72, 48,000 x 512: 37 / 38; 0.76, 100,000 x 1024: 135
+  // / 172; 1, 32,768 x 1024: 36 / 45.
+  const int64_t area = ((slots * tiles_m256 + cus - 1) / cus) * cus * kStreamBM * kStreamBN;
+  const bool fills = a.k_cand < 512 ? 4 * a.N * a.d_out >= 3 * area : 3 * a.N * a.d_out >= 2 * area;
+  const bool stream = can_stream && (fused || fills);
   RequestOut yr{static_cast<const bf16_t*>(a.w_rr), a.b_rr, static_cast<bf16_t*>(a.y_req),
                 (int)a.d_req, a.y_req != nullptr ? (int)((a.d_req + 15) / 16) : 0, (int)a.relu};
   // No candidates: only the Y^R tiles (the request table has no reader).
