@@ -67,3 +67,21 @@ def test_same_values_as_the_streaming_kernel(gpu_lib, counts, kc, d, act):
                               bias=dev_f32(c.bias), activation=act)
     torch.cuda.synchronize()
     assert torch.equal(got.view(torch.int16), stream.view(torch.int16))
+
+
+@pytest.mark.parametrize("kc", [448, 512], ids=["tiled", "streaming"])
+def test_rule_for_long_k(gpu_lib, kc):
+    # 2,900 x 4,096 fills 0.71 of one round of 256 x 256 tiles on 256 CUs:
+    # between the two shares of the rounds' area that decide below and from K 512.
+    c = wl.linear_case([1500, 0, 1399, 1], 24, kc, 4096, seed=kc, bias_std=0.2)
+    args = (dev_bf16(c.x_req), dev_bf16(c.x_cand), dev_bf16(c.w_req), dev_bf16(c.w_cand),
+            dev_i32(c.cand_offsets))
+    _, stream = gpu_lib.ikbo_linear_combined(*args, b_cand=dev_f32(c.bias), activation="relu")
+    got = gpu_lib.ikbo_linear(args[1], args[3], x_req=args[0], w_req=args[2],
+                              cand_offsets=args[4], bias=dev_f32(c.bias), activation="relu")
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), stream.view(torch.int16))
+    rows = np.array([0, 255, 256, 1499, 1500, 2047, 2898, 2899])
+    want = ikbo.ikbo_linear(c.x_req, c.x_cand[rows], c.w_req, c.w_cand, c.bias, None, "relu",
+                            request_map=ikbo.request_ids(c.cand_offsets)[rows])
+    assert_close(host(got)[rows], round_bf16(want), f"k{kc}")
