@@ -298,56 +298,83 @@ hipError_t dispatch_nk(const LcbArgs& a, hipStream_t s) {
 }
 
 // Request side, bf16 with E a multiple of 4: each thread makes 4 adjacent
-// embedding columns of one output row (8-byte input loads shared across the
-// 4 columns). At batch size R the kernel is bound by the latency of its loads:
-// the four waves of a workgroup split the fields, eight rows in flight each,
-// and reduce through LDS in a fixed order (16 requests, 128 fields of 128 ->
-// 96 rows: 17 -> 10 us).
+// embedding columns of NO stacked output rows (an 8-byte input load feeds 4 NO
+// products). At batch size R the kernel is bound by its loads' latency and
+// count: the four waves of a workgroup split the fields, up to 16 rows in
+// flight each, and reduce through LDS in a fixed order. VECW: four fields of a
+// weight row per load (F_r a multiple of 4, rows 8-byte aligned). Request plus
+// candidate side, one row with single weight loads / as chosen now: 65,536
+// candidates of 16 requests, 128 fields: 225 / 223.3 us; 8,000 of 22, 121
+// fields: 55.7 / 53.8; 1,500 of 3, 64 fields: 14.3 / 13.6 us.
+template <int NO, bool VECW>
 __global__ __launch_bounds__(256) void lcb_request_bf16x4(
     const bf16_t* __restrict__ xr, const bf16_t* __restrict__ wrr, const bf16_t* __restrict__ wcr,
     bf16_t* __restrict__ yr, float* __restrict__ z, int R, int FR, int OR, int OC, int E) {
-  constexpr int AHEAD = 8;
-  __shared__ f32x4 part[4][kWave];
+  constexpr int AHEAD = VECW || NO > 1 ? 16 : 8;
+  __shared__ f32x4 part[4][NO][kWave];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int E4 = E / 4;
-  const int64_t per_req = (int64_t)(OR + OC) * E4, total = R * per_req;
-  const int per_wave = (FR + 3) / 4;
-  const int f0 = wave * per_wave, f1 = min(f0 + per_wave, FR);
+  const int E4 = E / 4, O = OR + OC;
+  const int64_t per_req = (int64_t)((O + NO - 1) / NO) * E4, total = R * per_req;
+  const int per_wave = (FR + 15) / 16 * 4;
+  const int f0 = min(wave * per_wave, FR), f1 = min(f0 + per_wave, FR);
   for (int64_t base = (int64_t)blockIdx.x * kWave; base < total; base += (int64_t)gridDim.x * kWave) {
     const int64_t idx = min(base + lane, total - 1);      // clamped lanes never store
     const int r = (int)(idx / per_req);
-    const int o = (int)((idx % per_req) / E4), e = 4 * (int)(idx % E4);
-    const bool req_out = o < OR;
-    const bf16_t* w = req_out ? wrr + (int64_t)o * FR : wcr + (int64_t)(o - OR) * FR;
+    const int o0 = NO * (int)((idx % per_req) / E4), e = 4 * (int)(idx % E4);
     const bf16_t* x = xr + (int64_t)r * FR * E + e;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    const bf16_t* w[NO];
+#pragma unroll
+    for (int j = 0; j < NO; ++j) {
+      const int o = min(o0 + j, O - 1);
+      w[j] = o < OR ? wrr + (int64_t)o * FR : wcr + (int64_t)(o - OR) * FR;
+    }
+    f32x4 acc[NO];
+#pragma unroll
+    for (int j = 0; j < NO; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int f = f0; f < f1; f += AHEAD) {
-      u32x2 v[AHEAD];
-      float wf[AHEAD];
+      u32x2 v[AHEAD], wv[NO][AHEAD / 4];
 #pragma unroll
-      for (int j = 0; j < AHEAD; ++j) {
-        const int fj = min(f + j, f1 - 1);
-        v[j] = *reinterpret_cast<const u32x2*>(x + (int64_t)fj * E);
-        wf[j] = (float)w[fj];
-      }
+      for (int i = 0; i < AHEAD; ++i)
+        v[i] = *reinterpret_cast<const u32x2*>(x + (int64_t)min(f + i, f1 - 1) * E);
 #pragma unroll
-      for (int j = 0; j < AHEAD; ++j)
-        if (f + j < f1) {
-          acc[0] = fmaf(wf[j], bf16_lo(v[j][0]), acc[0]);
-          acc[1] = fmaf(wf[j], bf16_hi(v[j][0]), acc[1]);
-          acc[2] = fmaf(wf[j], bf16_lo(v[j][1]), acc[2]);
-          acc[3] = fmaf(wf[j], bf16_hi(v[j][1]), acc[3]);
+      for (int j = 0; j < NO; ++j)
+#pragma unroll
+        for (int i = 0; i < AHEAD / 4; ++i) {
+          if constexpr (VECW) {                           // f0, f1 and FR are multiples of four
+            wv[j][i] = *reinterpret_cast<const u32x2*>(w[j] + min(f + 4 * i, f1 - 4));
+          } else {
+            uint32_t b[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              b[u] = __builtin_bit_cast(uint16_t, w[j][min(f + 4 * i + u, f1 - 1)]);
+            wv[j][i] = u32x2{b[0] | b[1] << 16, b[2] | b[3] << 16};
+          }
+        }
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i)
+        if (f + i < f1) {
+#pragma unroll
+          for (int j = 0; j < NO; ++j) {
+            const uint32_t wp = wv[j][i / 4][i % 4 / 2];
+            const float wf = i % 2 ? bf16_hi(wp) : bf16_lo(wp);
+            acc[j][0] = fmaf(wf, bf16_lo(v[i][0]), acc[j][0]);
+            acc[j][1] = fmaf(wf, bf16_hi(v[i][0]), acc[j][1]);
+            acc[j][2] = fmaf(wf, bf16_lo(v[i][1]), acc[j][2]);
+            acc[j][3] = fmaf(wf, bf16_hi(v[i][1]), acc[j][3]);
+          }
         }
     }
-    part[wave][lane] = acc;
+#pragma unroll
+    for (int j = 0; j < NO; ++j) part[wave][j][lane] = acc[j];
     __syncthreads();
-    if (wave == 0 && base + lane < total) {
-      acc = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
-      if (req_out) {
+    const int o = o0 + wave;                              // wave j finishes output row j
+    if (wave < NO && base + lane < total && o < O) {
+      const f32x4 s = ((part[0][wave][lane] + part[1][wave][lane]) + part[2][wave][lane]) + part[3][wave][lane];
+      if (o < OR) {
         *reinterpret_cast<u32x2*>(yr + ((int64_t)r * OR + o) * E + e) =
-            u32x2{pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3])};
+            u32x2{pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3])};
       } else {
-        *reinterpret_cast<f32x4*>(z + ((int64_t)r * OC + (o - OR)) * E + e) = acc;
+        *reinterpret_cast<f32x4*>(z + ((int64_t)r * OC + (o - OR)) * E + e) = s;
       }
     }
     __syncthreads();                        // part is free for the next round
@@ -359,10 +386,23 @@ hipError_t launch_typed(const LcbArgs& a, bool fast, hipStream_t s) {
   hipError_t e;
   if (std::is_same_v<T, bf16_t> && fast) {
     // fast implies E in {64, 128} and 16-byte aligned rows
-    const int64_t req_waves = (a.R * (int64_t)(a.o_req + a.o_cand) * (a.emb / 4) + kWave - 1) / kWave;
-    if (!grid_fits(req_waves, 64)) return hipErrorInvalidConfiguration;
+    int cus = 0;
+    e = current_cu_count(&cus);
+    if (e != hipSuccess) return e;
+    const int64_t rows = a.o_req + a.o_cand;
+    const bool vecw = a.f_req % 4 == 0 && reinterpret_cast<uintptr_t>(a.w_cr) % 8 == 0 &&
+                      reinterpret_cast<uintptr_t>(a.w_rr) % 8 == 0;
+    // Four rows a thread once that still leaves every second CU a workgroup;
+    // 4 and 12 requests x 96 rows x 64 are faster with one (9.5 / 10.5, 13.6 / 14.3 us).
+    const bool four = a.R * rows * (a.emb / 4) >= (int64_t)2 * cus * kWave;
+    const int64_t per_req = (four ? (rows + 3) / 4 : rows) * (a.emb / 4);
+    const int64_t req_waves = (a.R * per_req + kWave - 1) / kWave;
     const int64_t blocks = req_waves < (1 << 22) ? req_waves : (1 << 22);   // they loop
-    e = launch_kernel(lcb_request_bf16x4, dim3((uint32_t)blocks), dim3(256),
+    e = launch_kernel(four && vecw ? lcb_request_bf16x4<4, true>
+                      : four ? lcb_request_bf16x4<4, false>
+                      : vecw ? lcb_request_bf16x4<1, true>
+                             : lcb_request_bf16x4<1, false>,
+                      dim3((uint32_t)blocks), dim3(256),
                       s, static_cast<const bf16_t*>(a.x_req), static_cast<const bf16_t*>(a.w_rr),
                       static_cast<const bf16_t*>(a.w_cr), static_cast<bf16_t*>(a.y_req), a.z,
                       (int)a.R, a.f_req, a.o_req, a.o_cand, a.emb);

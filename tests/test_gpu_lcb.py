@@ -3,6 +3,7 @@ explicit-broadcast LCB (Eq. glm-lcb-two-groups)."""
 
 import numpy as np
 import pytest
+import torch
 
 from gpu_util import assert_close, dev_bf16, dev_f32, dev_i32, host
 from oracle import ikbo
@@ -132,3 +133,29 @@ def test_lcb_deterministic_and_request_only(gpu_lib):
                              empty.cand_offsets)
     assert yc.shape == (0, 32, 128)
     assert_close(yr, round_bf16(want_r), "lcb request only")
+
+
+@pytest.mark.parametrize("reqs", [5, 90], ids=["few", "many"])
+@pytest.mark.parametrize("f_req,o_req,emb,shift", [
+    (1, 0, 64, 0), (3, 1, 128, 0), (4, 5, 64, 0), (6, 2, 128, 0), (16, 3, 64, 0), (20, 0, 128, 0),
+    (33, 7, 64, 0), (128, 64, 128, 0), (132, 6, 64, 0), (32, 5, 128, 1)])
+def test_lcb_request_edges(gpu_lib, f_req, o_req, emb, shift, reqs):
+    # Request side of the fast path: fields and output rows on and off the
+    # fours that a load and a thread take, waves without fields, and weight
+    # rows (shift 1) that are not 8-byte aligned. 90 requests take four rows a
+    # thread on 256 CUs.
+    case = wl.lcb_case([3, 0, 130, 1, 1] + [1] * (reqs - 5), f_req, 16, o_req, 32, emb, seed=f_req + o_req)
+
+    def weights(w):
+        buf = torch.zeros(w.size + shift, dtype=torch.bfloat16, device="cuda")
+        buf[shift:] = dev_bf16(w).reshape(-1)
+        return buf[shift:].view(*w.shape)
+
+    yr, yc = ops.ikbo_lcb(dev_bf16(case.x_req), dev_bf16(case.x_cand), weights(case.w_cr),
+                          dev_bf16(case.w_cc), dev_i32(case.cand_offsets),
+                          w_rr=None if case.w_rr is None else weights(case.w_rr))
+    want_r, want_c = ikbo.glm_lcb(case.x_req, case.x_cand, case.w_rr, case.w_cr, case.w_cc,
+                                  case.cand_offsets)
+    assert_close(host(yc), round_bf16(want_c), "y_cand")
+    if want_r is not None:
+        assert_close(host(yr), round_bf16(want_r), "y_req")
