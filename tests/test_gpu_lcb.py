@@ -159,3 +159,13 @@ def test_lcb_request_edges(gpu_lib, f_req, o_req, emb, shift, reqs):
     assert_close(host(yc), round_bf16(want_c), "y_cand")
     if want_r is not None:
         assert_close(host(yr), round_bf16(want_r), "y_req")
+
+
+@pytest.mark.parametrize("n", [2, 1023, 1025, 2047, 2049, 3073, 4097])
+def test_lcb_candidate_runs(gpu_lib, n):
+    # Runs of 1 to 4 candidates a wave on 256 CUs, with short last runs.
+    case = wl.lcb_case([n // 3, 0, n - n // 3], 8, 16, 0, 32, 64, seed=n)
+    _, yc = _run(case)
+    _, want = ikbo.glm_lcb(case.x_req, case.x_cand, case.w_rr, case.w_cr, case.w_cc,
+                           case.cand_offsets)
+    assert_close(yc, round_bf16(want), f"N {n}")
