@@ -1157,9 +1157,12 @@ hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
   // more: 0.25, 8,192 x 512: 54 / 37; 0.51, 50,000 x 512: 60 / 48; 0.67, 8,192
   // x 8,192: 92 / 117; 0.72, 48,000 x 512: 37 / 38; 0.76, 100,000 x 1024: 135
   // / 172; 1, 32,768 x 1024: 36 / 45.
-  const int64_t area = ((slots * tiles_m256 + cus - 1) / cus) * cus * kStreamBM * kStreamBN;
-  const bool fills = a.k_cand < 512 ? 4 * a.N * a.d_out >= 3 * area : 3 * a.N * a.d_out >= 2 * area;
-  const bool stream = can_stream && (fused || fills);
+  // (Only for calls that can stream: their sizes keep the products in 64 bits.)
+  auto fills = [&]() {
+    const int64_t area = ((slots * tiles_m256 + cus - 1) / cus) * cus * kStreamBM * kStreamBN;
+    return a.k_cand < 512 ? 4 * a.N * a.d_out >= 3 * area : 3 * a.N * a.d_out >= 2 * area;
+  };
+  const bool stream = can_stream && (fused || fills());
   RequestOut yr{static_cast<const bf16_t*>(a.w_rr), a.b_rr, static_cast<bf16_t*>(a.y_req),
                 (int)a.d_req, a.y_req != nullptr ? (int)((a.d_req + 15) / 16) : 0, (int)a.relu};
   // No candidates: only the Y^R tiles (the request table has no reader).
