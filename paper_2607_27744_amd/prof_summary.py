@@ -32,7 +32,7 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 # Kernel name substring -> source files that define it (hashed together).
 KERNEL_SOURCES = {
     "dca_attn_bf16": ["csrc/attention.hip", "csrc/common.h"],
-    "ikbo_gemm_bf16": ["csrc/linear.hip", "csrc/common.h"],
+    "ikbo_gemm_tile": ["csrc/linear.hip", "csrc/common.h"],
     "ikbo_gemm_stream": ["csrc/linear.hip", "csrc/common.h"],
     "glm_fm_bf16": ["csrc/interaction.hip", "csrc/common.h"],
 }
