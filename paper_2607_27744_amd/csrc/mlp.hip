@@ -48,6 +48,7 @@ namespace {
 constexpr int kMlpBM = 128;          // candidates per tile
 constexpr int kMlpHC = 64;           // hidden units per chunk
 constexpr int kMlpMaxHidden = 1024;
+constexpr int kMlpSmall = 32;        // candidates per workgroup of the small kernel
 
 // Chunk position of 16-byte chunk c of an LDS row: c ^ swizzle(row). With
 // 16 or more chunks per row the 16 rows read by a quarter-wave at one chunk
@@ -358,12 +359,197 @@ void ikbo_mlp2_bf16(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1,
   }
 }
 
+// Few candidates: the persistent kernel's 128-candidate tiles would leave most
+// CUs idle, each walking the chunks behind a barrier. Here a workgroup (eight
+// waves) takes 32 candidates and the whole hidden layer at once:
+//   1. wave w forms the 32-unit blocks w, w + 8, .. of H^T, X^C rows in
+//      registers, and writes them to LDS as bf16;
+//   2. after one barrier, wave w adds a 32-unit output block over all of H;
+//      with 128 outputs the two wave quartets split H and add up in LDS.
+// Each wave streams its weights through a private two-slot LDS ring of DMA
+// units (32 rows x 64 columns), one stream over both products. Bound by the
+// latency and the L2 reads of the weights. One request of 500 candidates, 256
+// -> 512 -> 256, request table included: 11.3 us (persistent kernel 21.6; the
+// weights loaded straight into registers, 32 lines touched per load: 29.5).
+template <int KC, int DO>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void ikbo_mlp2_small(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1,
+                     const float* __restrict__ zb, int64_t zb_stride,
+                     const bf16_t* __restrict__ w2, const float* __restrict__ b2,
+                     const int32_t* __restrict__ off, int R, int64_t N, int DH, int relu1,
+                     int relu2, bf16_t* __restrict__ out) {
+  constexpr int KS = KC / 16, JU = KC / 64, SPLIT = 256 / DO;
+  constexpr int ROWX = 2 * KC, CPRX = ROWX / 16;
+  constexpr int UB = 32 * 128;                    // bytes of a unit
+  // H rows are 16 bytes longer than the hidden layer: the rows that a
+  // quarter-wave reads at one chunk start in distinct 16-byte bank groups.
+  constexpr int HB = kMlpSmall * (2 * kMlpMaxHidden + 16);
+  static_assert(HB % 1024 == 512 && HB >= kMlpSmall * ROWX && HB >= 16 * 1024, "LDS plan");
+  constexpr int RO = HB + 512;                    // the rings, 1 KiB aligned
+  __shared__ __attribute__((aligned(1024))) char lds[RO + 8 * 2 * UB];
+  const uint32_t lbase = lds_addr(lds);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, hh = lane >> 5;
+  const int64_t n0 = (int64_t)blockIdx.x * kMlpSmall, n_at = n0 + l32;
+  const int64_t n = min(n_at, N - 1);             // rows past the end are never stored
+  const int stride = 2 * DH + 16;
+  const int blocks = DH / 32;
+  const int ob = SPLIT == 1 ? wave : wave & 3, half = SPLIT == 1 ? 0 : wave >> 2;
+
+  // The wave's units: its hidden blocks' JU each, then its 64-column units of W2.
+  const int n1 = wave < blocks ? (blocks - wave + 7) / 8 * JU : 0;
+  const int first2 = half == 0 ? 0 : (DH / 64 + 1) / 2;
+  const int last2 = SPLIT == 2 && half == 0 ? (DH / 64 + 1) / 2 : DH / 64;
+  const int units = n1 + last2 - first2;
+  const uint32_t ring = (uint32_t)(RO + wave * 2 * UB);
+  auto issue = [&](int u) __attribute__((always_inline)) {
+    const bool one = u < n1;
+    const bf16_t* rows = one ? w1 + (int64_t)32 * (wave + 8 * (u / JU)) * KC
+                             : w2 + (int64_t)32 * ob * DH;
+    const int col = one ? u % JU : first2 + u - n1;
+    const uint32_t rowb = one ? 2 * KC : 2 * DH;
+    const char* base = uniform_ptr(reinterpret_cast<const char*>(rows + 64 * col));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 8 * i + (lane >> 3);
+      lds_dma16_sv(base, (uint32_t)r * rowb + 16u * ((lane & 7) ^ mlp_swizzle<8>(r)),
+                   lbase + ring + (uint32_t)((u & 1) * UB) + 1024u * i);
+    }
+  };
+  // X^C rows through H's place, while the first units are on the way.
+#pragma unroll
+  for (int i = wave; i < kMlpSmall * ROWX / 1024; i += 8) {
+    const int p = 64 * i + lane, r = p / CPRX, pos = p % CPRX;
+    lds_dma16_sv(uniform_ptr(reinterpret_cast<const char*>(x + n0 * KC)),
+                 (uint32_t)((int)(min(n0 + r, N - 1) - n0) * ROWX + 16 * (pos ^ mlp_swizzle<CPRX>(r))),
+                 lbase + 1024u * i);
+  }
+  if (units > 0) issue(0);
+  if (units > 1) issue(1);
+  const float* zrow = zb;
+  if (off != nullptr) zrow = zb + (int64_t)owner_of(off, R, n) * zb_stride;
+  wait_vmcnt<0>();
+  __syncthreads();
+  bf16x8 xf[KS];
+#pragma unroll
+  for (int k = 0; k < KS; ++k)
+    xf[k] = *reinterpret_cast<const bf16x8*>(
+        lds + l32 * ROWX + 16 * ((2 * k + hh) ^ mlp_swizzle<CPRX>(l32)));
+  __syncthreads();                                // H's place is free
+
+  // Unit u's fragments; the next unit stays in flight, the one after starts.
+  bf16x8 wf[4];
+  auto take = [&](int u) __attribute__((always_inline)) {
+    if (u + 1 < units) wait_vmcnt<4>(); else wait_vmcnt<0>();
+    asm volatile("" ::: "memory");                // no read above the wait
+    const char* slot = lds + ring + (u & 1) * UB + l32 * 128;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      wf[k] = *reinterpret_cast<const bf16x8*>(slot + 16 * ((2 * k + hh) ^ mlp_swizzle<8>(l32)));
+    asm volatile("" ::: "memory");                // no read below the next one
+    wait_lgkmcnt0();                              // the slot has been read
+    asm volatile("" ::: "memory");
+    if (u + 2 < units) issue(u + 2);
+  };
+
+  const float lo1 = relu1 ? 0.f : -__builtin_inff();
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  int u = 0;
+  for (int hb = wave; hb < blocks; hb += 8) {
+    f32x16 acc = f32x16{};
+    if (zb != nullptr) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 z = *reinterpret_cast<const f32x4*>(zrow + 32 * hb + 8 * q + 4 * hh);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[4 * q + i] = z[i];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < JU; ++j, ++u) {
+      take(u);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc = mfma32(wf[k], xf[4 * j + k], acc);
+    }
+    uint32_t p[4][2];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) pack4(acc, q, zero, lo1, p[q][0], p[q][1]);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      *reinterpret_cast<u32x4*>(lds + l32 * stride + 2 * (32 * hb + 16 * j + 8 * hh)) =
+          swap_halves(p, j);
+  }
+
+  f32x16 acc = f32x16{};
+  if (b2 != nullptr && half == 0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 b = *reinterpret_cast<const f32x4*>(b2 + 32 * ob + 8 * q + 4 * hh);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[4 * q + i] = b[i];
+    }
+  }
+  __syncthreads();                                // H is whole
+  for (int c = first2; c < last2; ++c, ++u) {
+    bf16x8 hf[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      hf[k] = *reinterpret_cast<const bf16x8*>(lds + l32 * stride + 128 * c + 32 * k + 16 * hh);
+    take(u);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc = mfma32(wf[k], hf[k], acc);
+  }
+  if constexpr (SPLIT == 2) {
+    __syncthreads();                              // H has been read: its place is free
+    // 64 lanes x 64 bytes a wave, 16 KiB in all; the shortest H takes 4.5 KiB
+    // of the same array, whose size does not depend on it.
+    f32x4* part = reinterpret_cast<f32x4*>(lds) + ob * 256;
+    if (half == 1) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        part[64 * q + lane] = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    }
+    __syncthreads();
+    if (half == 1) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 v = part[64 * q + lane];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[4 * q + i] += v[i];
+    }
+  }
+  const float lo2 = relu2 ? 0.f : -__builtin_inff();
+  uint32_t p[4][2];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) pack4(acc, q, zero, lo2, p[q][0], p[q][1]);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const u32x4 v = swap_halves(p, j);            // every lane takes part in the swap
+    if (n_at < N)
+      *reinterpret_cast<u32x4*>(out + n_at * DO + 32 * ob + 16 * j + 8 * hh) = v;
+  }
+}
+
 template <int KC, int DO>
 hipError_t launch_fused(const Mlp2Args& a, const float* zb, int64_t zb_stride,
                         const int32_t* off, hipStream_t s) {
   int cus = 0;
   const hipError_t e = current_cu_count(&cus);
   if (e != hipSuccess) return e;
+  // Up to two rounds of 32-candidate workgroups (one fits a CU) beat the
+  // persistent kernel's weight stream through barriers. Persistent / small, us:
+  // 8,000 candidates, 256 -> 512 -> 256: 22.4 / 12.8, 128 -> 960 -> 256: 25.8 /
+  // 16.0; 12,000: 23.9 / 21.0, 27.0 / 26.9; 16,384: 25.0 / 22.5, 28.6 / 28.3.
+  // A round adds about 10 us, the persistent kernel's step to 24,000 0.3.
+  if (a.N <= (int64_t)2 * kMlpSmall * cus) {
+    return launch_kernel(ikbo_mlp2_small<KC, DO>, dim3((uint32_t)((a.N + kMlpSmall - 1) / kMlpSmall)),
+                         dim3(512), s, static_cast<const bf16_t*>(a.x_cand),
+                         static_cast<const bf16_t*>(a.w1_cand), zb, zb_stride,
+                         static_cast<const bf16_t*>(a.w2), a.b2, off, (int)a.R, a.N,
+                         (int)a.d_hidden, (int)a.relu1, (int)a.relu2,
+                         static_cast<bf16_t*>(a.out));
+  }
   const int64_t tiles = (a.N + kMlpBM - 1) / kMlpBM;
   const int grid = (int)(tiles < cus ? tiles : cus);
   return launch_kernel(ikbo_mlp2_bf16<KC, DO>, dim3((uint32_t)grid), dim3(512), s,

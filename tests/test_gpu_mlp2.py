@@ -118,3 +118,19 @@ def test_repeated_calls_and_empty(gpu_lib):
                         x_req=dev_bf16(c.x_req), w1_req=dev_bf16(c.w1_req),
                         cand_offsets=dev_i32(np.zeros(3, dtype=np.int32)))
     assert out.shape == (0, 128)
+
+
+@pytest.mark.parametrize("k_cand,d_h,d_o", [(128, 64, 128), (256, 64, 256), (128, 192, 256),
+                                            (256, 320, 128), (128, 960, 128), (256, 1024, 256)])
+@pytest.mark.parametrize("counts", [[1], [31, 0, 2], [32, 1] * 20 + [7], [5000, 0, 3193], [16384], [16380, 5]],
+                         ids=lambda c: f"N{sum(c)}-R{len(c)}")
+def test_few_candidates(gpu_lib, counts, k_cand, d_h, d_o):
+    # 32-candidate workgroups, two for each CU at most (16,384 candidates on 256
+    # CUs), and one candidate past one and two rounds: hidden layers of two blocks to the largest, rows
+    # past the end, requests that end inside a workgroup.
+    c = wl.mlp2_case(counts, 16, k_cand, d_h, d_o, seed=sum(counts) + d_h)
+    got = _run(c, activation2="relu")
+    np.testing.assert_array_equal(_run(c, activation2="relu"), got)
+    rows = np.unique(np.concatenate([np.arange(min(c.n_cand, 96)), [c.n_cand - 1],
+                                     np.random.default_rng(1).integers(0, c.n_cand, 200)]))
+    assert_close(got[rows], _want(c, act2="relu", rows=rows), f"{counts} {k_cand} {d_h} {d_o}")
