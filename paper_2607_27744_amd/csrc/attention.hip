@@ -632,10 +632,14 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(D == 64 
 // such a call leaves most CUs idle, and each workgroup walks the whole history
 // alone; here there are four times the workgroups, each a quarter of the walk.
 // Every wave stages K and V in LDS of its own (DMA, the next K under the
-// softmax, the next V under the next scores), so the waves meet only to merge
-// their partial softmaxes at the end. The layouts, the weights rounded to bf16
-// and the row sums taken from them are those of the tiled kernel; the running
-// max moves at every stage.
+// softmax, the next V under the next scores), so the waves meet only for the
+// first stage's row max and to merge their partial softmaxes at the end. The
+// layouts, the weights rounded to bf16, the row sums taken from them and the
+// running max are those of the tiled kernel: all four waves start from the row
+// max of the history's first stage and move it under the same rule, so a
+// weight is rounded against the same max in both kernels and their results
+// differ only by the order of fp32 sums (after a jump of the scores by more
+// than 2^kLazyRescale also by that max: a wave knows its own stages' alone).
 // What bounds it: the latency of a wave's chain of stages. At one request of
 // 203 candidates, history 613, 4 heads x 64 it takes 6.4 us (128-row tiles:
 // 11.7 us), at 16 requests of 32 query rows, history 1024: 7.7 us (15.4 us).
@@ -658,7 +662,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
   constexpr int OP = D + 4;                           // floats of one partial output row
   static_assert(TR * OP * 4 <= 2 * STAGE, "a wave's partial output takes its staging");
   __shared__ __attribute__((aligned(1024))) char lds[W * 2 * STAGE];
-  __shared__ float pm[W][TR], pl[W][TR];
+  __shared__ float pm[W][TR], pl[W][TR], m0[TR];
   ROCS_LDS char* const lds3 = (ROCS_LDS char*)lds;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -772,6 +776,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
   if (wave < ntiles) {
     issue(kbase, wave, kdst);
     issue(vbase, wave, kdst + STAGE);
+  } else {
+    ring_barrier();                                       // the first stage's row max, below
   }
   for (int t = wave; t < ntiles; t += W) {
     const bool more = t + W < ntiles;
@@ -798,32 +804,61 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         for (int e = 0; e < 16; ++e)
           if (32 * kb + 8 * (e / 4) + 4 * hh + e % 4 >= valid) sacc[kb][e] = -INFINITY;
     }
-    float mx = sacc[0][0];
+    // Row max: 32 keys per lane in two chains, then across the wave halves.
+    auto row_max = [&]() __attribute__((always_inline)) {
+      float mx[KB];
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
+      for (int kb = 0; kb < KB; ++kb) {
+        mx[kb] = sacc[kb][0];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sacc[kb][e]);
-    const float mn = fmaxf(m, max_across_halves(mx) * scale_log2);
-    const float ms = mn == -INFINITY ? 0.f : mn;          // no finite score yet: weights 0
-    const float alpha = exp2f(m - ms);
-    m = mn;
-    l_part *= alpha;
-#pragma unroll
-    for (int db = 0; db < DB; ++db) oacc[db] *= alpha;
-    // Each packed pair is a scalar of its own (see exp_block above).
-    uint32_t pk[PS][4];
-    const bf16x2 ones = {(bf16_t)1.0f, (bf16_t)1.0f};
-#pragma unroll
-    for (int ps = 0; ps < PS; ++ps)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const float s0 = sacc[ps / 2][8 * (ps % 2) + 2 * w];
-        const float s1 = sacc[ps / 2][8 * (ps % 2) + 2 * w + 1];
-        pk[ps][w] = pack_bf16x2(__builtin_amdgcn_exp2f(fmaf(s0, scale_log2, -ms)),
-                                __builtin_amdgcn_exp2f(fmaf(s1, scale_log2, -ms)));
-        l_part = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[ps][w]), ones,
-                                                 l_part, false);
+        for (int e = 1; e < 16; ++e) mx[kb] = fmaxf(mx[kb], sacc[kb][e]);
       }
+      static_assert(KB == 2, "two chains");
+      return max_across_halves(fmaxf(mx[0], mx[1])) * scale_log2;
+    };
+    if (t < W) {                                          // every wave's first stage
+      if (t == 0) {
+        const float mx = row_max();
+        if (hh == 0) m0[l32] = mx;
+        wait_lgkmcnt0();
+      }
+      ring_barrier();
+      m = m0[l32];
+    }
+    // Each packed pair is a scalar of its own (see exp_block above); a sum per
+    // 16 keys, so that the test of the weights waits for a short chain.
+    uint32_t pk[PS][4];
+    auto weights = [&](float ms) __attribute__((always_inline)) {
+      const bf16x2 ones = {(bf16_t)1.0f, (bf16_t)1.0f};
+      float part[PS];
+#pragma unroll
+      for (int ps = 0; ps < PS; ++ps) {
+        part[ps] = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const float s0 = sacc[ps / 2][8 * (ps % 2) + 2 * w];
+          const float s1 = sacc[ps / 2][8 * (ps % 2) + 2 * w + 1];
+          pk[ps][w] = pack_bf16x2(__builtin_amdgcn_exp2f(fmaf(s0, scale_log2, -ms)),
+                                  __builtin_amdgcn_exp2f(fmaf(s1, scale_log2, -ms)));
+          part[ps] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[ps][w]), ones,
+                                                     part[ps], false);
+        }
+      }
+      static_assert(PS == 4, "four sums");
+      return (part[0] + part[1]) + (part[2] + part[3]);
+    };
+    float lst = weights(m);
+    if (__builtin_expect(__ballot(!(lst <= kWeightBound)) != 0, 0)) {
+      const float mx = row_max();
+      const bool need = mx > m + kLazyRescale;
+      const float alpha = need ? exp2f(m - mx) : 1.f;
+      if (need) m = mx;
+      l_part *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) oacc[db] *= alpha;
+      lst = weights(m == -INFINITY ? 0.f : m);            // no finite score yet: weights 0
+    }
+    l_part += lst;
     if (more) wait_vmcnt<NI>(); else wait_vmcnt<0>();     // V of t (K of t + 4 in flight)
     asm volatile("" ::: "memory");
 #pragma unroll

@@ -449,7 +449,17 @@ def test_split_history(gpu_lib, head_dim, q_len, scale):
         dev_bf16(np.concatenate([case.q] * more)), dev_bf16(np.concatenate([case.k] * more)),
         dev_bf16(np.concatenate([case.v] * more)), dev_i32(wl.offsets_from_counts(counts * more)),
         dev_i32(wl.offsets_from_counts(lens * more)), scale=scale)
-    assert_close(host(big)[:n], got, "tiled kernel", atol=8e-3, rtol=1.6e-2)   # 2 bf16 ulps
+    a = host(big)[:n]
+    assert_close(a, got, "tiled kernel", atol=8e-3, rtol=1.6e-2)   # 2 bf16 ulps
+    if scale is None:
+        # Without jumps of the scores by 64 binary orders both kernels round a
+        # weight against the same running max and differ by the order of fp32
+        # sums alone: at most an ulp of bf16 (2^-7 of a value), and only where
+        # the sum lies that close to a rounding boundary. The sums' difference
+        # is about 1e-5 of the largest partial sum at random signs (at most
+        # 1030 * 2^-24), an ulp 2^-8 to 2^-7: under 1 value in 100.
+        assert np.mean(a != got) < 0.01
+        assert_close(a, got, "tiled kernel", atol=1e-5, rtol=2.0 ** -7, normwise=5e-4)
 
 
 def test_split_history_infinite_scores(gpu_lib):
