@@ -8,8 +8,7 @@
 // that ops.py's checks accept; for anything else (other argument types, a
 // failed check, an exception from the tensor library) it returns None and
 // ops.py's own path runs, which raises the error or handles the call. Nothing
-// is kept between calls except the Python callables and type objects looked
-// up at import.
+// is kept between calls except the Python callables looked up at import.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -32,7 +31,8 @@ void need(bool ok) {
   if (!ok) throw Refuse();
 }
 
-// A tensor argument: plain strided device tensors only; null for None.
+// A tensor argument: plain strided device tensors with storage of their own
+// only (not torch.func's wrappers); null for None.
 struct Ten {
   const at::Tensor* t = nullptr;
   at::Tensor own;
@@ -53,7 +53,7 @@ struct Call {
     if (o == Py_None) return r;
     need(THPVariable_CheckExact(o));
     r.t = &THPVariable_Unpack(o);
-    need(r.t->is_cuda() && r.t->layout() == c10::kStrided);
+    need(r.t->is_cuda() && r.t->layout() == c10::kStrided && r.t->has_storage());
     if (!any) dev = r.t->device();
     any = true;
     need(r.t->device() == dev);
@@ -148,12 +148,23 @@ void bias_of(const Ten& t, int64_t n) {
               t->is_contiguous()));
 }
 
-template <typename F>
-void run(const char* name, F call) {
+// Without the interpreter lock for its lifetime, however the scope is left.
+struct Unlocked {
+  PyThreadState* state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+// Calls the C entry point without the interpreter lock. Every pointer and size
+// is an argument here, so it has been taken while the lock was held: data_ptr()
+// throws for a tensor without storage (inside torch.vmap or torch.func.grad).
+template <typename... P, typename... A>
+void run(const char* name, int32_t (*call)(P...), A... args) {
+  static_assert(sizeof...(P) == sizeof...(A), "argument count");
   int32_t status;
-  Py_BEGIN_ALLOW_THREADS
-  status = call();
-  Py_END_ALLOW_THREADS
+  {
+    Unlocked unlocked;
+    status = call(args...);
+  }
   if (status == ROCS_OK) return;
   PyObject* r = PyObject_CallFunction(g_check, "is", (int)status, name);
   Py_XDECREF(r);
@@ -234,16 +245,12 @@ PyObject* linear(PyObject* const* a) {
   if (!ws && bytes > 0) ws = c.or_new(Py_None, {(int64_t)bytes}, c10::kByte);
   void* s = stream_of(a[11]);
   if (mapped)
-    run("rocs_ikbo_linear_mapped", [&] {
-      return rocs_ikbo_linear_mapped(xr.ptr(), kr, x.ptr(), add.ptr(), k, wr.ptr(), w.ptr(),
-                                     bias.f32(), index.i32(), r, n, d, code, act, data(out),
-                                     data(ws), nbytes(ws), s);
-    });
+    run("rocs_ikbo_linear_mapped", rocs_ikbo_linear_mapped, xr.ptr(), kr, x.ptr(), add.ptr(), k,
+        wr.ptr(), w.ptr(), bias.f32(), index.i32(), r, n, d, code, act, data(out), data(ws),
+        nbytes(ws), s);
   else
-    run("rocs_ikbo_linear", [&] {
-      return rocs_ikbo_linear(xr.ptr(), kr, x.ptr(), add.ptr(), k, wr.ptr(), w.ptr(), bias.f32(),
-                              index.i32(), r, n, d, code, act, data(out), data(ws), nbytes(ws), s);
-    });
+    run("rocs_ikbo_linear", rocs_ikbo_linear, xr.ptr(), kr, x.ptr(), add.ptr(), k, wr.ptr(),
+        w.ptr(), bias.f32(), index.i32(), r, n, d, code, act, data(out), data(ws), nbytes(ws), s);
   return result(a[9], out);
 }
 
@@ -274,11 +281,9 @@ PyObject* glm_linear(PyObject* const* a) {
   Ten ws = c.get(a[12]);
   if (!ws && bytes > 0) ws = c.or_new(Py_None, {(int64_t)bytes}, c10::kByte);
   void* s = stream_of(a[13]);
-  run("rocs_glm_linear", [&] {
-    return rocs_glm_linear(xr.ptr(), kr, x.ptr(), add.ptr(), k, wrr.ptr(), wr.ptr(), w.ptr(),
-                           br.f32(), bias.f32(), off.i32(), r, n, dr, d, code, act, data(yr),
-                           data(out), data(ws), nbytes(ws), s);
-  });
+  run("rocs_glm_linear", rocs_glm_linear, xr.ptr(), kr, x.ptr(), add.ptr(), k, wrr.ptr(), wr.ptr(),
+      w.ptr(), br.f32(), bias.f32(), off.i32(), r, n, dr, d, code, act, data(yr), data(out),
+      data(ws), nbytes(ws), s);
   return pair(result(a[10], yr), result(a[11], out));
 }
 
@@ -311,11 +316,9 @@ PyObject* mlp2(PyObject* const* a) {
   Ten ws = c.get(a[11]);
   if (!ws && bytes > 0) ws = c.or_new(Py_None, {(int64_t)bytes}, c10::kByte);
   void* s = stream_of(a[12]);
-  run("rocs_ikbo_mlp2", [&] {
-    return rocs_ikbo_mlp2(xr.ptr(), kr, x.ptr(), k, wr.ptr(), w1.ptr(), b1.f32(), w2.ptr(),
-                          b2.f32(), off.i32(), r, n, dh, d, code, act1, act2, data(out), data(ws),
-                          nbytes(ws), s);
-  });
+  run("rocs_ikbo_mlp2", rocs_ikbo_mlp2, xr.ptr(), kr, x.ptr(), k, wr.ptr(), w1.ptr(), b1.f32(),
+      w2.ptr(), b2.f32(), off.i32(), r, n, dh, d, code, act1, act2, data(out), data(ws), nbytes(ws),
+      s);
   return result(a[10], out);
 }
 
@@ -342,11 +345,9 @@ PyObject* fm_linear(PyObject* const* a) {
   Ten ws = c.get(a[8]);
   if (!ws && bytes > 0) ws = c.or_new(Py_None, {(int64_t)bytes}, c10::kByte);
   void* s = stream_of(a[9]);
-  run("rocs_glm_fm_linear", [&] {
-    return rocs_glm_fm_linear(xr.ptr(), x.ptr(), off.i32(), r, n, (int32_t)fr, (int32_t)fc,
-                              (int32_t)e, wr.ptr(), w.ptr(), bias.f32(), d, code, act, data(out),
-                              data(ws), nbytes(ws), s);
-  });
+  run("rocs_glm_fm_linear", rocs_glm_fm_linear, xr.ptr(), x.ptr(), off.i32(), r, n, (int32_t)fr,
+      (int32_t)fc, (int32_t)e, wr.ptr(), w.ptr(), bias.f32(), d, code, act, data(out), data(ws),
+      nbytes(ws), s);
   return result(a[7], out);
 }
 
@@ -383,17 +384,13 @@ PyObject* lcb(PyObject* const* a) {
   if (!ws) ws = c.or_new(Py_None, {(int64_t)(bytes > 0 ? bytes : 1)}, c10::kByte);
   void* s = stream_of(a[10]);
   if (mapped)
-    run("rocs_ikbo_lcb_mapped", [&] {
-      return rocs_ikbo_lcb_mapped(xr.ptr(), x.ptr(), wrr.ptr(), wcr.ptr(), wcc.ptr(), index.i32(),
-                                  r, n, (int32_t)fr, (int32_t)fc, (int32_t)orq, (int32_t)oc,
-                                  (int32_t)e, code, data(yr), data(yc), data(ws), nbytes(ws), s);
-    });
+    run("rocs_ikbo_lcb_mapped", rocs_ikbo_lcb_mapped, xr.ptr(), x.ptr(), wrr.ptr(), wcr.ptr(),
+        wcc.ptr(), index.i32(), r, n, (int32_t)fr, (int32_t)fc, (int32_t)orq, (int32_t)oc,
+        (int32_t)e, code, data(yr), data(yc), data(ws), nbytes(ws), s);
   else
-    run("rocs_ikbo_lcb", [&] {
-      return rocs_ikbo_lcb(xr.ptr(), x.ptr(), wrr.ptr(), wcr.ptr(), wcc.ptr(), index.i32(), r, n,
-                           (int32_t)fr, (int32_t)fc, (int32_t)orq, (int32_t)oc, (int32_t)e, code,
-                           data(yr), data(yc), data(ws), nbytes(ws), s);
-    });
+    run("rocs_ikbo_lcb", rocs_ikbo_lcb, xr.ptr(), x.ptr(), wrr.ptr(), wcr.ptr(), wcc.ptr(),
+        index.i32(), r, n, (int32_t)fr, (int32_t)fc, (int32_t)orq, (int32_t)oc, (int32_t)e, code,
+        data(yr), data(yc), data(ws), nbytes(ws), s);
   PyObject* first = Py_None;
   if (orq > 0) first = result(a[7], yr);
   else Py_INCREF(first);
@@ -414,10 +411,8 @@ PyObject* plan(PyObject* const* a) {
   if (p) need(p->scalar_type() == c10::kByte && p->is_contiguous() && p->numel() >= bytes);
   else p = c.or_new(Py_None, {bytes}, c10::kByte);
   void* s = stream_of(a[6]);
-  run("rocs_dca_attention_plan", [&] {
-    return rocs_dca_attention_plan(co.i32(), ko.i32(), r, n, (int32_t)q, (int32_t)h, data(p),
-                                   nbytes(p), s);
-  });
+  run("rocs_dca_attention_plan", rocs_dca_attention_plan, co.i32(), ko.i32(), r, n, (int32_t)q,
+      (int32_t)h, data(p), nbytes(p), s);
   return result(a[5], p);
 }
 
@@ -479,34 +474,26 @@ PyObject* attention(PyObject* const* a) {
     Ten ws = c.get(a[13]);
     if (!ws && bytes > 0) ws = c.or_new(Py_None, {(int64_t)bytes}, c10::kByte);
     void* s = stream_of(a[14]);
-    run("rocs_dca_attention_mapped", [&] {
-      return rocs_dca_attention_mapped(q.ptr(), k.ptr(), v.ptr(), ids.i32(), ko.i32(), r, n,
-                                       (int32_t)t, (int32_t)h, (int32_t)d, stride, scale, code,
-                                       data(out), data(ws), nbytes(ws), s);
-    });
+    run("rocs_dca_attention_mapped", rocs_dca_attention_mapped, q.ptr(), k.ptr(), v.ptr(),
+        ids.i32(), ko.i32(), r, n, (int32_t)t, (int32_t)h, (int32_t)d, stride, scale, code,
+        data(out), data(ws), nbytes(ws), s);
     return result(a[11], out);
   }
   void* s = stream_of(a[14]);
   if (a[15] != Py_True) {
     need(!wq && !pl);
     if (res)
-      run("rocs_dca_attention_residual", [&] {
-        return rocs_dca_attention_residual(q.ptr(), k.ptr(), v.ptr(), co.i32(), ko.i32(), r, n,
-                                           (int32_t)t, (int32_t)h, (int32_t)d, stride, scale, code,
-                                           res.ptr(), data(out), data(sum), s);
-      });
+      run("rocs_dca_attention_residual", rocs_dca_attention_residual, q.ptr(), k.ptr(), v.ptr(),
+          co.i32(), ko.i32(), r, n, (int32_t)t, (int32_t)h, (int32_t)d, stride, scale, code,
+          res.ptr(), data(out), data(sum), s);
     else
-      run("rocs_dca_attention", [&] {
-        return rocs_dca_attention(q.ptr(), k.ptr(), v.ptr(), co.i32(), ko.i32(), r, n, (int32_t)t,
-                                  (int32_t)h, (int32_t)d, stride, scale, code, data(out), s);
-      });
+      run("rocs_dca_attention", rocs_dca_attention, q.ptr(), k.ptr(), v.ptr(), co.i32(), ko.i32(),
+          r, n, (int32_t)t, (int32_t)h, (int32_t)d, stride, scale, code, data(out), s);
     return res ? pair(result(a[11], out), result(a[12], sum)) : result(a[11], out);
   }
-  run("rocs_dca_attention_ex", [&] {
-    return rocs_dca_attention_ex(q.ptr(), d_in, wq.ptr(), k.ptr(), v.ptr(), co.i32(), ko.i32(),
-                                 pl.ptr(), pl.bytes(), r, n, (int32_t)t, (int32_t)h, (int32_t)d,
-                                 stride, scale, code, res.ptr(), data(out), data(sum), s);
-  });
+  run("rocs_dca_attention_ex", rocs_dca_attention_ex, q.ptr(), d_in, wq.ptr(), k.ptr(), v.ptr(),
+      co.i32(), ko.i32(), pl.ptr(), pl.bytes(), r, n, (int32_t)t, (int32_t)h, (int32_t)d, stride,
+      scale, code, res.ptr(), data(out), data(sum), s);
   return res ? pair(result(a[11], out), result(a[12], sum)) : result(a[11], out);
 }
 
