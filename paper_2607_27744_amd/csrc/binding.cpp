@@ -44,9 +44,35 @@ struct Ten {
   size_t bytes() const { return t == nullptr ? 0 : (size_t)t->nbytes(); }
 };
 
+// The address in a Python integer (a new reference, or null after an error).
+void* address(PyObject* v) {
+  if (v == nullptr) throw PyError();
+  void* p = PyLong_AsVoidPtr(v);
+  Py_DECREF(v);
+  if (p == nullptr && PyErr_Occurred()) throw PyError();
+  return p;
+}
+
+// The current stream of a device (its number, a new reference).
+void* current_stream(PyObject* device) {
+  if (device == nullptr) throw PyError();
+  PyObject* v = PyObject_CallOneArg(g_raw_stream, device);
+  Py_DECREF(device);
+  return address(v);
+}
+
+// The given stream, or the current one of the current device.
+void* stream_of(PyObject* o) {
+  if (o == Py_None) return current_stream(PyObject_CallNoArgs(g_get_device));
+  return address(PyObject_GetAttr(o, g_cuda_stream));
+}
+
 struct Call {
   c10::Device dev{c10::DeviceType::CPU};
   bool any = false;
+  PyObject* stream;
+
+  explicit Call(PyObject* s) : stream(s) {}
 
   Ten get(PyObject* o) {
     Ten r;
@@ -67,6 +93,8 @@ struct Call {
   Ten or_new(PyObject* o, c10::IntArrayRef shape, c10::ScalarType type) {
     Ten r = get(o);
     if (!r) {
+      // Memory for a call on another stream is that stream's: ops.py takes it.
+      need(stream == Py_None || stream_of(stream) == current_stream(PyLong_FromLong(dev.index())));
       r.own = at::empty(shape, c10::TensorOptions().dtype(type).device(dev));
       return r;
     }
@@ -112,24 +140,6 @@ float scale_of(PyObject* o) {           // float(scale or 0.0)
     throw Refuse();
   }
   return (float)v;
-}
-
-// The given stream, or the current one of the current device.
-void* stream_of(PyObject* o) {
-  PyObject* v;
-  if (o == Py_None) {
-    PyObject* d = PyObject_CallNoArgs(g_get_device);
-    if (d == nullptr) throw PyError();
-    v = PyObject_CallOneArg(g_raw_stream, d);
-    Py_DECREF(d);
-  } else {
-    v = PyObject_GetAttr(o, g_cuda_stream);
-  }
-  if (v == nullptr) throw PyError();
-  void* p = PyLong_AsVoidPtr(v);
-  Py_DECREF(v);
-  if (p == nullptr && PyErr_Occurred()) throw PyError();
-  return p;
 }
 
 void offsets(const Ten& t, int64_t n_req) {
@@ -212,7 +222,7 @@ PyObject* entry(PyObject*, PyObject* const* args, Py_ssize_t n) {
 // x_cand, w_cand, x_req, w_req, index, mapped, bias, activation, x_cand_add,
 // out, workspace, stream
 PyObject* linear(PyObject* const* a) {
-  Call c;
+  Call c(a[11]);
   const Ten x = c.must(a[0]), w = c.must(a[1]), xr = c.get(a[2]), wr = c.get(a[3]),
             index = c.get(a[4]), bias = c.get(a[6]), add = c.get(a[8]);
   const bool mapped = a[5] == Py_True;
@@ -243,7 +253,7 @@ PyObject* linear(PyObject* const* a) {
   const size_t bytes = rocs_ikbo_linear_workspace_size(r, n, d, kr);
   Ten ws = c.get(a[10]);
   if (!ws && bytes > 0) ws = c.or_new(Py_None, {(int64_t)bytes}, c10::kByte);
-  void* s = stream_of(a[11]);
+  void* s = stream_of(c.stream);
   if (mapped)
     run("rocs_ikbo_linear_mapped", rocs_ikbo_linear_mapped, xr.ptr(), kr, x.ptr(), add.ptr(), k,
         wr.ptr(), w.ptr(), bias.f32(), index.i32(), r, n, d, code, act, data(out), data(ws),
@@ -257,7 +267,7 @@ PyObject* linear(PyObject* const* a) {
 // x_req, x_cand, w_rr, w_cr, w_cc, cand_offsets, b_req, b_cand, activation,
 // x_cand_add, y_req, y_cand, workspace, stream
 PyObject* glm_linear(PyObject* const* a) {
-  Call c;
+  Call c(a[13]);
   const Ten xr = c.must(a[0]), x = c.must(a[1]), wrr = c.must(a[2]), wr = c.must(a[3]),
             w = c.must(a[4]), off = c.must(a[5]), br = c.get(a[6]), bias = c.get(a[7]),
             add = c.get(a[9]);
@@ -280,7 +290,7 @@ PyObject* glm_linear(PyObject* const* a) {
   const size_t bytes = rocs_ikbo_linear_workspace_size(r, n, d, kr);
   Ten ws = c.get(a[12]);
   if (!ws && bytes > 0) ws = c.or_new(Py_None, {(int64_t)bytes}, c10::kByte);
-  void* s = stream_of(a[13]);
+  void* s = stream_of(c.stream);
   run("rocs_glm_linear", rocs_glm_linear, xr.ptr(), kr, x.ptr(), add.ptr(), k, wrr.ptr(), wr.ptr(),
       w.ptr(), br.f32(), bias.f32(), off.i32(), r, n, dr, d, code, act, data(yr), data(out),
       data(ws), nbytes(ws), s);
@@ -290,7 +300,7 @@ PyObject* glm_linear(PyObject* const* a) {
 // x_cand, w1_cand, w2, x_req, w1_req, cand_offsets, b1, b2, activation1,
 // activation2, out, workspace, stream
 PyObject* mlp2(PyObject* const* a) {
-  Call c;
+  Call c(a[12]);
   const Ten x = c.must(a[0]), w1 = c.must(a[1]), w2 = c.must(a[2]), xr = c.get(a[3]),
             wr = c.get(a[4]), off = c.get(a[5]), b1 = c.get(a[6]), b2 = c.get(a[7]);
   const int32_t act1 = activation(a[8]), act2 = activation(a[9]);
@@ -315,7 +325,7 @@ PyObject* mlp2(PyObject* const* a) {
   const size_t bytes = rocs_ikbo_mlp2_workspace_size(r, n, kr, k, dh, d, code);
   Ten ws = c.get(a[11]);
   if (!ws && bytes > 0) ws = c.or_new(Py_None, {(int64_t)bytes}, c10::kByte);
-  void* s = stream_of(a[12]);
+  void* s = stream_of(c.stream);
   run("rocs_ikbo_mlp2", rocs_ikbo_mlp2, xr.ptr(), kr, x.ptr(), k, wr.ptr(), w1.ptr(), b1.f32(),
       w2.ptr(), b2.f32(), off.i32(), r, n, dh, d, code, act1, act2, data(out), data(ws), nbytes(ws),
       s);
@@ -325,7 +335,7 @@ PyObject* mlp2(PyObject* const* a) {
 // x_req, x_cand, cand_offsets, w_req, w_cand, bias, activation, out,
 // workspace, stream
 PyObject* fm_linear(PyObject* const* a) {
-  Call c;
+  Call c(a[9]);
   const Ten xr = c.must(a[0]), x = c.must(a[1]), off = c.must(a[2]), wr = c.must(a[3]),
             w = c.must(a[4]), bias = c.get(a[5]);
   const int32_t act = activation(a[6]);
@@ -344,7 +354,7 @@ PyObject* fm_linear(PyObject* const* a) {
                                                          (int32_t)e, d, code);
   Ten ws = c.get(a[8]);
   if (!ws && bytes > 0) ws = c.or_new(Py_None, {(int64_t)bytes}, c10::kByte);
-  void* s = stream_of(a[9]);
+  void* s = stream_of(c.stream);
   run("rocs_glm_fm_linear", rocs_glm_fm_linear, xr.ptr(), x.ptr(), off.i32(), r, n, (int32_t)fr,
       (int32_t)fc, (int32_t)e, wr.ptr(), w.ptr(), bias.f32(), d, code, act, data(out), data(ws),
       nbytes(ws), s);
@@ -354,7 +364,7 @@ PyObject* fm_linear(PyObject* const* a) {
 // x_req, x_cand, w_rr, w_cr, w_cc, index, mapped, y_req, y_cand, workspace,
 // stream
 PyObject* lcb(PyObject* const* a) {
-  Call c;
+  Call c(a[10]);
   const Ten xr = c.must(a[0]), x = c.must(a[1]), wrr = c.get(a[2]), wcr = c.must(a[3]),
             wcc = c.must(a[4]), index = c.must(a[5]);
   const bool mapped = a[6] == Py_True;
@@ -382,7 +392,7 @@ PyObject* lcb(PyObject* const* a) {
   const size_t bytes = rocs_ikbo_lcb_workspace_size(r, oc, e);
   Ten ws = c.get(a[9]);
   if (!ws) ws = c.or_new(Py_None, {(int64_t)(bytes > 0 ? bytes : 1)}, c10::kByte);
-  void* s = stream_of(a[10]);
+  void* s = stream_of(c.stream);
   if (mapped)
     run("rocs_ikbo_lcb_mapped", rocs_ikbo_lcb_mapped, xr.ptr(), x.ptr(), wrr.ptr(), wcr.ptr(),
         wcc.ptr(), index.i32(), r, n, (int32_t)fr, (int32_t)fc, (int32_t)orq, (int32_t)oc,
@@ -399,7 +409,7 @@ PyObject* lcb(PyObject* const* a) {
 
 // cand_offsets, kv_offsets, num_cand, heads, q_len, plan, stream
 PyObject* plan(PyObject* const* a) {
-  Call c;
+  Call c(a[6]);
   const Ten co = c.must(a[0]), ko = c.must(a[1]);
   const int64_t n = integer(a[2]), h = integer(a[3]), q = integer(a[4]);
   need(h >= 0 && h <= INT32_MAX && q >= 0 && q <= INT32_MAX);
@@ -410,7 +420,7 @@ PyObject* plan(PyObject* const* a) {
   Ten p = c.get(a[5]);
   if (p) need(p->scalar_type() == c10::kByte && p->is_contiguous() && p->numel() >= bytes);
   else p = c.or_new(Py_None, {bytes}, c10::kByte);
-  void* s = stream_of(a[6]);
+  void* s = stream_of(c.stream);
   run("rocs_dca_attention_plan", rocs_dca_attention_plan, co.i32(), ko.i32(), r, n, (int32_t)q,
       (int32_t)h, data(p), nbytes(p), s);
   return result(a[5], p);
@@ -419,7 +429,7 @@ PyObject* plan(PyObject* const* a) {
 // q (or x), w_q, heads, k, v, cand_offsets, ids, kv_offsets, plan, residual,
 // scale, out, out_sum, workspace, stream, ex (the extended entry point)
 PyObject* attention(PyObject* const* a) {
-  Call c;
+  Call c(a[14]);
   const Ten q = c.must(a[0]), wq = c.get(a[1]), k = c.must(a[3]), v = c.must(a[4]),
             co = c.get(a[5]), ids = c.get(a[6]), ko = c.must(a[7]), pl = c.get(a[8]),
             res = c.get(a[9]);
@@ -473,13 +483,13 @@ PyObject* attention(PyObject* const* a) {
     const size_t bytes = rocs_dca_attention_mapped_workspace_size(r, n);
     Ten ws = c.get(a[13]);
     if (!ws && bytes > 0) ws = c.or_new(Py_None, {(int64_t)bytes}, c10::kByte);
-    void* s = stream_of(a[14]);
+    void* s = stream_of(c.stream);
     run("rocs_dca_attention_mapped", rocs_dca_attention_mapped, q.ptr(), k.ptr(), v.ptr(),
         ids.i32(), ko.i32(), r, n, (int32_t)t, (int32_t)h, (int32_t)d, stride, scale, code,
         data(out), data(ws), nbytes(ws), s);
     return result(a[11], out);
   }
-  void* s = stream_of(a[14]);
+  void* s = stream_of(c.stream);
   if (a[15] != Py_True) {
     need(!wq && !pl);
     if (res)

@@ -75,6 +75,27 @@ def _need(cond, msg):
         raise ValueError(msg)
 
 
+def _new(shape, dtype, device, stream, scratch=False):
+    """A tensor for a call on `stream`. The allocator hands freed memory on in
+    the order of the stream that it was allocated under, so for a call on
+    another stream than the current one it comes from that stream's memory: the
+    kernels run after its earlier uses, and a workspace (scratch) goes back
+    after them. An output is also marked as used on the current stream, where
+    its owner may read and free it."""
+    if stream is not None and device.type == "cuda":
+        current = torch.cuda.current_stream(device)
+        if stream.cuda_stream != current.cuda_stream:
+            if not isinstance(stream, torch.cuda.Stream):
+                stream = (torch.cuda.ExternalStream(stream.cuda_stream, device)
+                          if stream.cuda_stream else torch.cuda.default_stream(device))
+            with torch.cuda.stream(stream):
+                t = torch.empty(shape, dtype=dtype, device=device)
+            if not scratch:
+                t.record_stream(current)
+            return t
+    return torch.empty(shape, dtype=dtype, device=device)
+
+
 def _on_gpu(*ts):
     dev = None
     for t in ts:
@@ -170,7 +191,7 @@ def ikbo_linear_combined(x_req, x_cand, w_cr, w_cc, cand_offsets, *, w_rr=None, 
             _need(b_req.dtype == torch.float32 and b_req.shape == (d_req,),
                   "b_req must be float32 [d_req]")
         if y_req is None:
-            y_req = torch.empty((n_req, d_req), dtype=x_req.dtype, device=x_req.device)
+            y_req = _new((n_req, d_req), x_req.dtype, x_req.device, stream)
         _need(y_req.shape == (n_req, d_req) and y_req.dtype == x_req.dtype and
               y_req.is_contiguous(), "y_req must be a contiguous [R, d_req] tensor")
         _on_gpu(w_rr, b_req, y_req)
@@ -199,7 +220,7 @@ def glm_linear(x_req, x_cand, w_rr, w_cr, w_cc, cand_offsets, *, b_req=None, b_c
     if b_req is not None:
         _need(b_req.dtype == torch.float32 and b_req.shape == (d_req,), "b_req must be float32 [d_req]")
     if y_req is None:
-        y_req = torch.empty((n_req, d_req), dtype=x_req.dtype, device=x_req.device)
+        y_req = _new((n_req, d_req), x_req.dtype, x_req.device, stream)
     _need(y_req.shape == (n_req, d_req) and y_req.dtype == x_req.dtype and y_req.is_contiguous(),
           "y_req must be a contiguous [R, d_req] tensor")
     _on_gpu(x_req, w_rr, b_req, y_req)
@@ -241,12 +262,12 @@ def _linear(x_cand, w_cand, x_req, w_req, cand_offsets, cand_ids, mapped, bias, 
     for t in (x_cand, w_cand, x_req, w_req, x_cand_add, bias):
         _need(t is None or t.is_contiguous(), "tensors must be contiguous")
     if out is None:
-        out = torch.empty((n_cand, d_out), dtype=x_cand.dtype, device=x_cand.device)
+        out = _new((n_cand, d_out), x_cand.dtype, x_cand.device, stream)
     _need(out.shape == (n_cand, d_out) and out.dtype == x_cand.dtype and out.is_contiguous(),
           "out must be a contiguous [N, d_out] tensor of the input dtype")
     need = int(lib.rocs_ikbo_linear_workspace_size(n_req, n_cand, d_out, k_req))
     if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x_cand.device)
+        workspace = _new(need, torch.uint8, x_cand.device, stream, scratch=True)
     _on_gpu(x_cand, w_cand, x_req, w_req, index, bias, x_cand_add, out, workspace)
     _need(activation in _ACT, f"activation must be one of {sorted(k for k in _ACT if k)}")
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
@@ -319,13 +340,13 @@ def ikbo_mlp2(x_cand, w1_cand, w2, *, x_req=None, w1_req=None, cand_offsets=None
     for t in (x_cand, w1_cand, w2, x_req, w1_req, b1, b2):
         _need(t is None or t.is_contiguous(), "tensors must be contiguous")
     if out is None:
-        out = torch.empty((n_cand, d_out), dtype=x_cand.dtype, device=x_cand.device)
+        out = _new((n_cand, d_out), x_cand.dtype, x_cand.device, stream)
     _need(out.shape == (n_cand, d_out) and out.dtype == x_cand.dtype and out.is_contiguous(),
           "out must be a contiguous [N, d_out] tensor of the input dtype")
     need = int(lib.rocs_ikbo_mlp2_workspace_size(n_req, n_cand, k_req, k_cand, d_hidden, d_out,
                                                  code))
     if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x_cand.device)
+        workspace = _new(need, torch.uint8, x_cand.device, stream, scratch=True)
     _on_gpu(x_cand, w1_cand, w2, x_req, w1_req, cand_offsets, b1, b2, out, workspace)
     for a in (activation1, activation2):
         _need(a in _ACT, f"activation must be one of {sorted(k for k in _ACT if k)}")
@@ -372,13 +393,13 @@ def glm_fm_linear(x_req, x_cand, cand_offsets, w_req, w_cand, *, bias=None, acti
     for t in (x_req, x_cand, w_req, w_cand, bias):
         _need(t is None or t.is_contiguous(), "tensors must be contiguous")
     if out is None:
-        out = torch.empty((n_cand, d_out), dtype=x_cand.dtype, device=x_cand.device)
+        out = _new((n_cand, d_out), x_cand.dtype, x_cand.device, stream)
     _need(out.shape == (n_cand, d_out) and out.dtype == x_cand.dtype and out.is_contiguous(),
           "out must be a contiguous [N, d_out] tensor of the input dtype")
     need = int(lib.rocs_glm_fm_linear_workspace_size(n_req, n_cand, f_req, f_cand, emb, d_out,
                                                      code))
     if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x_cand.device)
+        workspace = _new(need, torch.uint8, x_cand.device, stream, scratch=True)
     _on_gpu(x_req, x_cand, cand_offsets, w_req, w_cand, bias, out, workspace)
     _need(activation in _ACT, f"activation must be one of {sorted(k for k in _ACT if k)}")
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
@@ -423,7 +444,7 @@ def dca_attention_plan(cand_offsets, kv_offsets, *, num_cand, heads, q_len=1, pl
     _offsets(cand_offsets, n_req)
     need = dca_attention_plan_size(n_req)
     if plan is None:
-        plan = torch.empty(need, dtype=torch.uint8, device=kv_offsets.device)
+        plan = _new(need, torch.uint8, kv_offsets.device, stream)
     _need(plan.dtype == torch.uint8 and plan.is_contiguous() and plan.numel() >= need,
           f"plan must be a contiguous uint8 tensor of at least {need} bytes")
     _on_gpu(cand_offsets, kv_offsets, plan)
@@ -470,14 +491,14 @@ def dca_attention_ex(q, k, v, cand_offsets, kv_offsets, *, w_q=None, heads=None,
     _offsets(cand_offsets, n_req)
     shape = (n_cand, q_len, heads, dim)
     if out is None:
-        out = torch.empty(shape, dtype=q.dtype, device=q.device)
+        out = _new(shape, q.dtype, q.device, stream)
     _need(tuple(out.shape) == shape and out.dtype == q.dtype and out.is_contiguous(),
           "out must be [N, T, heads, d] of q's dtype")
     if residual is not None:
         _need(tuple(residual.shape) == shape and residual.dtype == q.dtype and
               residual.is_contiguous(), "residual must be a contiguous [N, T, heads, d] tensor")
         if out_sum is None:
-            out_sum = torch.empty_like(out)
+            out_sum = _new(shape, q.dtype, q.device, stream)
         _need(out_sum.shape == out.shape and out_sum.dtype == out.dtype and
               out_sum.is_contiguous(), "out_sum must match out")
     if plan is not None:
@@ -566,7 +587,7 @@ def _attention(q, k, v, cand_offsets, cand_ids, kv_offsets, scale, out, stream, 
     else:
         _offsets(cand_offsets, n_req)
     if out is None:
-        out = torch.empty_like(q)
+        out = _new(q.shape, q.dtype, q.device, stream)
     _need(out.shape == q.shape and out.dtype == q.dtype and out.is_contiguous(),
           "out must match q")
     _on_gpu(q, k, v, cand_offsets, cand_ids, kv_offsets, out)
@@ -575,7 +596,7 @@ def _attention(q, k, v, cand_offsets, cand_ids, kv_offsets, scale, out, stream, 
         _need(residual.shape == q.shape and residual.dtype == q.dtype and
               residual.is_contiguous(), "residual must be a contiguous tensor shaped like q")
         if out_sum is None:
-            out_sum = torch.empty_like(q)
+            out_sum = _new(q.shape, q.dtype, q.device, stream)
         _need(out_sum.shape == q.shape and out_sum.dtype == q.dtype and out_sum.is_contiguous(),
               "out_sum must match q")
         _on_gpu(residual, out_sum)
@@ -587,7 +608,7 @@ def _attention(q, k, v, cand_offsets, cand_ids, kv_offsets, scale, out, stream, 
     if mapped:
         need = int(lib.rocs_dca_attention_mapped_workspace_size(n_req, n_cand))
         if workspace is None and need > 0:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+            workspace = _new(need, torch.uint8, q.device, stream, scratch=True)
         _on_gpu(workspace)
         ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
         _lib.check(lib.rocs_dca_attention_mapped(
@@ -614,10 +635,9 @@ def glm_interaction(x_req, x_cand, cand_offsets, *, request_side=True, candidate
     _need(x_req.is_contiguous() and x_cand.is_contiguous(), "inputs must be contiguous")
     _offsets(cand_offsets, n_req)
     if request_side and y_req is None:
-        y_req = torch.empty((n_req, f_req * f_req), dtype=x_req.dtype, device=x_req.device)
+        y_req = _new((n_req, f_req * f_req), x_req.dtype, x_req.device, stream)
     if candidate_side and y_cand is None:
-        y_cand = torch.empty((n_cand, f_cand * (f_req + f_cand)), dtype=x_req.dtype,
-                             device=x_req.device)
+        y_cand = _new((n_cand, f_cand * (f_req + f_cand)), x_req.dtype, x_req.device, stream)
     for t, shape in ((y_req, (n_req, f_req * f_req)),
                      (y_cand, (n_cand, f_cand * (f_req + f_cand)))):
         _need(t is None or (t.shape == shape and t.dtype == x_req.dtype and t.is_contiguous()),
@@ -673,16 +693,16 @@ def _lcb(x_req, x_cand, w_rr, w_cr, w_cc, cand_offsets, cand_ids, y_req, y_cand,
     else:
         _offsets(cand_offsets, n_req)
     if o_req > 0 and y_req is None:
-        y_req = torch.empty((n_req, o_req, emb), dtype=x_req.dtype, device=x_req.device)
+        y_req = _new((n_req, o_req, emb), x_req.dtype, x_req.device, stream)
     if y_cand is None:
-        y_cand = torch.empty((n_cand, o_cand, emb), dtype=x_req.dtype, device=x_req.device)
+        y_cand = _new((n_cand, o_cand, emb), x_req.dtype, x_req.device, stream)
     _need(y_cand.shape == (n_cand, o_cand, emb) and y_cand.dtype == x_req.dtype and
           y_cand.is_contiguous(), "y_cand must be a contiguous [N, O_c, E] tensor")
     _need(y_req is None or (y_req.shape == (n_req, o_req, emb) and y_req.dtype == x_req.dtype
                             and y_req.is_contiguous()), "y_req must be [R, O_r, E]")
     need = int(lib.rocs_ikbo_lcb_workspace_size(n_req, o_cand, emb))
     if workspace is None:
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=x_req.device)
+        workspace = _new(max(need, 1), torch.uint8, x_req.device, stream, scratch=True)
     _on_gpu(x_req, x_cand, w_rr, w_cr, w_cc, cand_offsets, cand_ids, y_req, y_cand, workspace)
     fn, name = ((lib.rocs_ikbo_lcb_mapped, "rocs_ikbo_lcb_mapped") if mapped
                 else (lib.rocs_ikbo_lcb, "rocs_ikbo_lcb"))
@@ -699,7 +719,7 @@ def request_ids(cand_offsets, num_cand, *, stream=None):
     lib = _lib.load()
     n_req = cand_offsets.numel() - 1
     _offsets(cand_offsets, n_req)
-    out = torch.empty(num_cand, dtype=torch.int32, device=cand_offsets.device)
+    out = _new(num_cand, torch.int32, cand_offsets.device, stream)
     _on_gpu(cand_offsets, out)
     _lib.check(lib.rocs_request_ids(_ptr(cand_offsets), n_req, num_cand, _ptr(out),
                                     _stream(stream)), "rocs_request_ids")
