@@ -547,19 +547,30 @@ def dca_request_attention(q_req, k, v, kv_offsets, *, scale=None, out=None, stre
     _need(q_req.dim() == 4, "q_req must be [R, T, H, d]")
     n_req = q_req.shape[0]
     _need(kv_offsets.numel() == n_req + 1, "kv_offsets needs R + 1 entries")
-    return _attention(q_req, k, v, _identity_offsets(n_req, q_req.device), None, kv_offsets,
+    return _attention(q_req, k, v, _identity_offsets(n_req, q_req.device, stream), None, kv_offsets,
                       scale, out, stream)
 
 
 _IDENTITY = {}
 
 
-def _identity_offsets(n_req, device):
-    """[0, 1, ..., R] int32 on the device, built once per (R, device)."""
-    key = (n_req, str(device))
+def _identity_offsets(n_req, device, stream):
+    """[0, 1, ..., R] int32 on the device: the front of an array built once per
+    (power of two, device), complete before any stream reads it. Under capture
+    an array that is not there yet becomes part of the graph instead, which
+    fills it on every replay."""
+    size = 1 << max(n_req + 1, 1024).bit_length()
+    key = (size, str(device))
     if key not in _IDENTITY:
-        _IDENTITY[key] = torch.arange(n_req + 1, dtype=torch.int32, device=device)
-    return _IDENTITY[key]
+        if device.type == "cuda" and torch.cuda.is_current_stream_capturing():
+            t = _new(n_req + 1, torch.int32, device, stream, scratch=True)
+            with torch.cuda.stream(stream):
+                return torch.arange(n_req + 1, dtype=torch.int32, device=device, out=t)
+        t = torch.arange(size, dtype=torch.int32, device=device)
+        if t.is_cuda:
+            torch.cuda.current_stream(device).synchronize()
+        _IDENTITY[key] = t
+    return _IDENTITY[key][:n_req + 1]
 
 
 def _attention(q, k, v, cand_offsets, cand_ids, kv_offsets, scale, out, stream, workspace=None,

@@ -63,3 +63,25 @@ def test_output_freed_on_the_current_stream(gpu_lib):
         again = torch.empty(512, 512, dtype=torch.bfloat16, device="cuda")
     assert not cur.query() and again.data_ptr() != at
     torch.cuda.synchronize()
+
+
+def test_identity_offsets_first_needed_under_capture(gpu_lib, monkeypatch):
+    # Request-side attention builds its offsets on first use. A graph's own
+    # memory, unwritten before its first replay, must not serve eager calls.
+    monkeypatch.setattr(ops, "_IDENTITY", {})
+    kw = _calls()["attention request"][1]
+    n = kw["q_req"].shape[0]
+    offsets = dict(cand_offsets=torch.arange(n + 1, dtype=torch.int32, device="cuda"))
+    want = ops.dca_attention(kw["q_req"], kw["k"], kw["v"], **offsets, kv_offsets=kw["kv_offsets"])
+    out = torch.empty_like(want)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ops.dca_request_attention(**kw, out=out)
+    assert not ops._IDENTITY
+    for _ in range(3):
+        assert torch.equal(ops.dca_request_attention(**kw), want)
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
