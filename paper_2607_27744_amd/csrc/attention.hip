@@ -920,31 +920,61 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
 // ---------------------------------------------------------------------------
 // General kernel: any dtype, head_dim <= 256, any stride.
 //
-// A workgroup takes 16 consecutive query rows of one head; its four waves
-// split the history in blocks of 16 keys and merge their partial softmaxes
-// through LDS. Scores and outputs run on the fp32 matrix instructions (fp32
-// in, fp32 accumulation; bf16 inputs convert exactly): S^T = K Q^T leaves
-// lane (l16, g) with keys 4 g .. + 3 of query row l16, which is the B operand
-// of O^T = V^T P^T as it stands, so the weights never leave the registers.
-// Rows of other requests in the tile (a request's edge, or a caller's map in
-// any order) take a pass of their own over their request's history; a pass
-// hands on only its own rows. Against one wave per query row with a
-// cross-lane sum per key (26 us at 256 rows x 2 heads x 32, history 32, fp32)
-// a tile reads K and V once for 16 rows and reduces across lanes once per 16
-// keys: 5 us.
+// A workgroup takes 16 consecutive query rows of one head; its four
+// waves split the history in blocks of 16 keys and merge their partial
+// softmaxes through LDS. Scores and outputs run on the fp32 matrix
+// instructions (fp32 in, fp32 accumulation; bf16 inputs convert exactly): S^T =
+// K Q^T leaves lane (l16, g) with keys 4 g .. + 3 of query row l16, which is
+// the B operand of O^T = V^T P^T as it stands, so the weights never leave the
+// registers. Rows of other requests in the tile (a request's edge, or a
+// caller's map in any order) take a pass of their own over their request's
+// history; a pass hands on only its own rows.
+// A score is summed in 4 CB accumulators, added pairwise: one chain over
+// head_dim would be less exact than a lane tree. Error against float64 (fp32,
+// 256 rows x 2 heads; a lane tree with keys in order / one chain / as here):
+// head_dim 32, history 32: 1.67e-7 / 1.80e-7 / 1.36e-7; 128, 32: 1.69e-7 /
+// 3.01e-7 / 1.38e-7; 256, 5: 9.05e-8 / 2.12e-7 / 9.03e-8; 64, 2000: 1.04e-6 /
+// 5.0e-7 / 4.3e-7. (bf16 inputs: four, the output's rounding hides the rest.)
+// What bounds it: the latency of a wave's loads. They are clamped and selected
+// rather than skipped, so that a block's K and V are in flight together, and
+// the registers leave room for two workgroups a CU: 8,192 rows x 2 heads x 128,
+// history 200, fp32: 104 -> 60 us; 64 rows x 4 heads x 64, history 5000: 335 ->
+// 117 us; 256 rows x 2 heads x 32, history 32: 4.9 -> 4.2 us (one wave per
+// query row: 809, 4018 and 20.5). fp32 at head_dim 256 needs one workgroup a CU
+// and K's loads in turn: 100 rows x 2 heads, history 700: 174 us, 236 with them
+// all in flight.
 // ---------------------------------------------------------------------------
 constexpr int kGenRows = 16;
+
+// Dims d .. d + 3 of a row of D, zeros past its end. The loads are clamped, not
+// skipped: a branch around each would keep them from being in flight together.
+template <typename T, bool VEC>
+__device__ __forceinline__ f32x4 dims4(const T* row, int d, int D) {
+  if constexpr (VEC) {                     // D is a multiple of four, and so is d
+    const f32x4 v = load4_f32<T, true>(row + min(d, D - 4), 4);
+    return d < D ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+  } else {
+    f32x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float x = load_f32(row + min(d + i, D - 1));
+      v[i] = d + i < D ? x : 0.f;
+    }
+    return v;
+  }
+}
 
 // DP: head_dim rounded up to 32, 64, 128 or 256. VEC: every row of q, k, x and
 // w_q is aligned to four elements and head_dim (and d_in) a multiple of four.
 template <typename T, int DP, bool VEC>
-__global__ __launch_bounds__(256) void dca_attn_generic(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP == 256 && sizeof(T) == 4 ? 1 : 2))) void dca_attn_generic(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const int32_t* __restrict__ cand_off, const int32_t* __restrict__ kv_off,
     T* __restrict__ out, int R, int Tq, int64_t n_rows, int H, int D, int64_t kv_stride,
     float scale, const int32_t* __restrict__ ids, const T* __restrict__ res,
     T* __restrict__ out_sum, const T* __restrict__ wq, int d_in) {
   constexpr int NB = DP / 16;              // 16-dim blocks
+  constexpr int CB = sizeof(T) == 2 || DP == 32 ? 1 : DP == 64 ? 4 : 8;
   constexpr int LP = DP + 4;               // LDS row (floats), padded against bank conflicts
   __shared__ __attribute__((aligned(16))) float po[4][kGenRows][LP];   // O, per wave (also Q)
   __shared__ float pm[4][kGenRows], pl[4][kGenRows];                   // running max, row sum
@@ -966,7 +996,7 @@ __global__ __launch_bounds__(256) void dca_attn_generic(
   if (wq == nullptr) {
     const T* qr = q + (row * H + h) * D;
 #pragma unroll
-    for (int b = 0; b < NB; ++b) qf[b] = load4_f32<T, VEC>(qr + 16 * b + 4 * g, D - 16 * b - 4 * g);
+    for (int b = 0; b < NB; ++b) qf[b] = dims4<T, VEC>(qr, 16 * b + 4 * g, D);
   } else {
     // The fused query projection q = x W_q^T for this head's dims, rounded to
     // T as a separate projection would store it; the waves share the blocks.
@@ -1004,13 +1034,26 @@ __global__ __launch_bounds__(256) void dca_attn_generic(
     for (int b = 0; b < NB; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int kb = 16 * wave; kb < L; kb += 64) {
       const T* kr = k + (a + min(kb + l16, L - 1)) * kv_stride + (int64_t)h * D;
-      f32x4 s4 = {0.f, 0.f, 0.f, 0.f};
+      const T* vr[4];                                    // clamped: no load waits for a branch
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        vr[i] = v + (a + min(kb + 4 * g + i, L - 1)) * kv_stride + (int64_t)h * D;
+      f32x4 part[CB][4] = {};
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-        const f32x4 kf = load4_f32<T, VEC>(kr + 16 * b + 4 * g, D - 16 * b - 4 * g);
+        const f32x4 kf = DP == 256 ? load4_f32<T, VEC>(kr + 16 * b + 4 * g, D - 16 * b - 4 * g)
+                                   : dims4<T, VEC>(kr, 16 * b + 4 * g, D);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s4 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i], qf[b][i], s4, 0, 0, 0);
+        for (int i = 0; i < 4; ++i)
+          part[b % CB][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i], qf[b][i], part[b % CB][i], 0, 0, 0);
       }
+#pragma unroll
+      for (int c = 1; c < CB; c *= 2)                    // pairwise
+#pragma unroll
+        for (int b = 0; b + c < CB; b += 2 * c)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) part[b][i] += part[b + c][i];
+      f32x4 s4 = (part[0][0] + part[0][1]) + (part[0][2] + part[0][3]);
       float mx = -INFINITY;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -1031,10 +1074,9 @@ __global__ __launch_bounds__(256) void dca_attn_generic(
         o[b] *= alpha;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int key = kb + 4 * g + i;
-          const float vf = key < L && dim < D
-                               ? load_f32(v + (a + key) * kv_stride + (int64_t)h * D + dim) : 0.f;
-          o[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf, p[i], o[b], 0, 0, 0);
+          const float vf = load_f32(vr[i] + min(dim, D - 1));
+          o[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(kb + 4 * g + i < L && dim < D ? vf : 0.f, p[i],
+                                                      o[b], 0, 0, 0);
         }
       }
     }
@@ -1052,21 +1094,29 @@ __global__ __launch_bounds__(256) void dca_attn_generic(
   }
   __syncthreads();
   // Merge the four partial softmaxes of each row. An empty history gives zeros.
-  for (int idx = threadIdx.x; idx < rows * D; idx += 256) {
-    const int i = idx / D, d = idx - i * D;
+  // Four dims a step: a row's four factors are formed once for them.
+  for (int idx = threadIdx.x; idx < rows * (DP / 4); idx += 256) {
+    const int i = idx / (DP / 4), d0 = 4 * (idx % (DP / 4));
+    if (d0 >= D) continue;
     const float mx = fmaxf(fmaxf(pm[0][i], pm[1][i]), fmaxf(pm[2][i], pm[3][i]));
     const float ms = mx == -INFINITY ? 0.f : mx;
-    float l = 0.f, y = 0.f;
+    float l = 0.f;
+    f32x4 y = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       const float f = expf(pm[w][i] - ms);
       l += pl[w][i] * f;
-      y += po[w][i][d] * f;
+      y += *reinterpret_cast<const f32x4*>(&po[w][i][d0]) * f;
     }
-    const T yt = from_f32<T>(has_keys[i] ? y * (1.0f / l) : 0.f);
-    const int64_t at = ((row0 + i) * H + h) * D + d;
-    out[at] = yt;
-    if (res != nullptr) out_sum[at] = from_f32<T>(load_f32(&yt) + load_f32(res + at));
+    const float inv = 1.0f / l;
+    const int64_t at = ((row0 + i) * H + h) * D + d0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (d0 + e >= D) break;
+      const T yt = from_f32<T>(has_keys[i] ? y[e] * inv : 0.f);
+      out[at + e] = yt;
+      if (res != nullptr) out_sum[at + e] = from_f32<T>(load_f32(&yt) + load_f32(res + at + e));
+    }
   }
 }
 
