@@ -920,7 +920,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
 // ---------------------------------------------------------------------------
 // General kernel: any dtype, head_dim <= 256, any stride.
 //
-// A workgroup takes 16 consecutive query rows of one head; its four
+// A workgroup takes up to 16 consecutive query rows of one head; its four
 // waves split the history in blocks of 16 keys and merge their partial
 // softmaxes through LDS. Scores and outputs run on the fp32 matrix
 // instructions (fp32 in, fp32 accumulation; bf16 inputs convert exactly): S^T =
@@ -944,7 +944,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
 // and K's loads in turn: 100 rows x 2 heads, history 700: 174 us, 236 with them
 // all in flight.
 // ---------------------------------------------------------------------------
-constexpr int kGenRows = 16;
+constexpr int kGenRows = 16;   // at most
 
 // Dims d .. d + 3 of a row of D, zeros past its end. The loads are clamped, not
 // skipped: a branch around each would keep them from being in flight together.
@@ -967,11 +967,12 @@ __device__ __forceinline__ f32x4 dims4(const T* row, int d, int D) {
 // DP: head_dim rounded up to 32, 64, 128 or 256. VEC: every row of q, k, x and
 // w_q is aligned to four elements and head_dim (and d_in) a multiple of four.
 template <typename T, int DP, bool VEC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP == 256 && sizeof(T) == 4 ? 1 : 2))) void dca_attn_generic(
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(DP == 256 && sizeof(T) == 4 ? 1 : 2))) void dca_attn_generic(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
     const int32_t* __restrict__ cand_off, const int32_t* __restrict__ kv_off,
-    T* __restrict__ out, int R, int Tq, int64_t n_rows, int H, int D, int64_t kv_stride,
-    float scale, const int32_t* __restrict__ ids, const T* __restrict__ res,
+    T* __restrict__ out, int R, int Tq, int64_t n_rows, int tile_rows, int H, int D,
+    int64_t kv_stride, float scale, const int32_t* __restrict__ ids, const T* __restrict__ res,
     T* __restrict__ out_sum, const T* __restrict__ wq, int d_in) {
   constexpr int NB = DP / 16;              // 16-dim blocks
   constexpr int CB = sizeof(T) == 2 || DP == 32 ? 1 : DP == 64 ? 4 : 8;
@@ -983,8 +984,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP == 256 &
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, g = lane >> 4;
   const int h = blockIdx.y;
-  const int64_t row0 = (int64_t)blockIdx.x * kGenRows;
-  const int rows = (int)(n_rows - row0 < kGenRows ? n_rows - row0 : kGenRows);
+  const int64_t row0 = (int64_t)blockIdx.x * tile_rows;
+  const int rows = (int)(n_rows - row0 < tile_rows ? n_rows - row0 : tile_rows);
   const int64_t row = row0 + min(l16, rows - 1);         // clamped; extra rows never stored
   // The row's request: from the caller's per-candidate map (clamped into
   // [0, R), so a malformed map gives wrong rows, never an access outside the
@@ -1045,7 +1046,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DP == 256 &
                                    : dims4<T, VEC>(kr, 16 * b + 4 * g, D);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          part[b % CB][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i], qf[b][i], part[b % CB][i], 0, 0, 0);
+          part[b % CB][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i], qf[b][i], part[b % CB][i],
+                                                                 0, 0, 0);
       }
 #pragma unroll
       for (int c = 1; c < CB; c *= 2)                    // pairwise
@@ -1527,7 +1529,29 @@ hipError_t launch_fast_mapped(const AttentionArgs& a, hipStream_t s) {
 template <typename T>
 hipError_t launch_generic(const AttentionArgs& a, hipStream_t s) {
   const int64_t rows = a.N * a.q_len;
-  const int64_t blocks = (rows + kGenRows - 1) / kGenRows;
+  // Rows per workgroup. Sixteen share every K and V read, but a tile takes one
+  // pass per request in it, one after the other: where its rows are of many
+  // requests and the chip has room, smaller tiles run the passes side by side.
+  // A map in any order mixes its requests: two rows from 8 requests on. CSR
+  // offsets mix them where a request has fewer than four rows: four rows, and
+  // also while even those leave CUs idle. Measured (us, 16 / 4 / 2 rows, fp32,
+  // 2 heads): map, 1,000 rows of 16 requests x 32, history 100: 27.9 / 15.8 /
+  // 15.1; 3,000 of 1,000 x 48, 30: 40.9 / 27.3 / 29.5; 256 of 8 x 256, 5: 51.4 /
+  // 26.5 / 15.1; 8,192 of 16 x 64, 200: 170 / 206 / 218; 4,000 of 16 x 256, 100:
+  // 316 / 443 / 464. CSR, 4 heads: 500 of 500 x 64, 200: 94 / 42 / 49; 2 heads:
+  // 1,000 of 16 x 32, 100 (126 tiles): 8.3 / 9.4; 256 of 1 x 32, 32: 4.2 / 3.7.
+  int cus = 0;
+  const hipError_t ce = current_cu_count(&cus);
+  if (ce != hipSuccess) return ce;
+  const int64_t tiles16 = (rows + 15) / 16 * a.heads;
+  const bool room = a.head_dim <= 128 ? tiles16 <= 2 * cus : 2 * tiles16 <= cus;
+  int tile_rows = 16;
+  if (a.ids != nullptr) {
+    if (a.R >= 8 && room) tile_rows = 2;
+  } else if ((rows < 4 * a.R && room) || 4 * tiles16 <= cus) {
+    tile_rows = 4;
+  }
+  const int64_t blocks = (rows + tile_rows - 1) / tile_rows;
   if (!grid_fits(blocks, 256) || a.heads > 65535) return hipErrorInvalidConfiguration;
   auto ok = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % (4 * sizeof(T)) == 0; };
   const bool vec = a.head_dim % 4 == 0 && a.kv_stride % 4 == 0 && ok(a.q) && ok(a.k) &&
@@ -1536,7 +1560,8 @@ hipError_t launch_generic(const AttentionArgs& a, hipStream_t s) {
     return launch_kernel(kernel, dim3((uint32_t)blocks, (uint32_t)a.heads), dim3(256), s,
                          static_cast<const T*>(a.q), static_cast<const T*>(a.k),
                          static_cast<const T*>(a.v), a.cand_offsets, a.kv_offsets,
-                         static_cast<T*>(a.out), (int)a.R, a.q_len, rows, a.heads, a.head_dim,
+                         static_cast<T*>(a.out), (int)a.R, a.q_len, rows, tile_rows, a.heads,
+                         a.head_dim,
                          a.kv_stride, a.scale, a.ids, static_cast<const T*>(a.residual),
                          static_cast<T*>(a.out_sum), static_cast<const T*>(a.proj_w), a.proj_in);
   };

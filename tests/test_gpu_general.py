@@ -148,3 +148,36 @@ def test_attention_general_is_as_exact_as_a_lane_tree(gpu_lib, dim, length):
         return np.linalg.norm(y - want) / np.linalg.norm(want)
 
     assert error(got) <= 1.02 * error(_lane_tree(q, k, v).astype(np.float64))
+
+
+@pytest.mark.parametrize("n_req,n,heads,q_len,dim", [
+    (8, 37, 2, 1, 32), (8, 35, 1, 3, 250),          # two rows a workgroup
+    (7, 37, 2, 1, 48), (9, 700, 12, 1, 16),         # sixteen: few requests, many rows
+    (3, 9, 1, 1, 256)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_attention_general_mapped(gpu_lib, n_req, n, heads, q_len, dim, dtype):
+    # A map in any order: every row of a workgroup may be of another request.
+    bf = dtype == "bf16"
+    rng = np.random.default_rng(n + dim)
+    lens = rng.integers(0, 70, n_req)
+    lens[0], lens[-1] = 0, 17
+    c = wl.attention_case([n] + [0] * (n_req - 1), lens, heads, dim, q_len=q_len, seed=dim, bf16=bf)
+    ids = rng.integers(0, n_req, n).astype(np.int32)
+    dev = dev_bf16 if bf else dev_f32
+    got = host(gpu_lib.dca_attention_mapped(dev(c.q), dev(c.k), dev(c.v), dev_i32(ids),
+                                            dev_i32(c.kv_offsets)))
+    order = np.argsort(ids, kind="stable")
+    off = np.concatenate([[0], np.cumsum(np.bincount(ids, minlength=n_req))])
+    want = np.empty(c.q.shape)
+    want[order] = ikbo.dca_attention(c.q[order], c.k, c.v, off, c.kv_offsets, mode="explicit")
+    assert_close(got, want, f"R{n_req} d{dim}", **({} if bf else F32))
+
+
+def test_attention_general_few_rows_a_request(gpu_lib):
+    # Four rows a workgroup, rows of up to four requests in each.
+    c = wl.attention_case([1, 2, 0, 3, 1, 1, 1, 2], [5, 64, 3, 17, 0, 1, 70, 33], 2, 40, seed=4,
+                          bf16=False)
+    got = host(gpu_lib.dca_attention(dev_f32(c.q), dev_f32(c.k), dev_f32(c.v),
+                                     dev_i32(c.cand_offsets), dev_i32(c.kv_offsets)))
+    want = ikbo.dca_attention(c.q, c.k, c.v, c.cand_offsets, c.kv_offsets, mode="explicit")
+    assert_close(got, want, "few rows", **F32)
