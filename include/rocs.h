@@ -57,6 +57,8 @@ typedef enum rocs_status {
 
 typedef enum rocs_dtype { ROCS_DTYPE_F32 = 0, ROCS_DTYPE_BF16 = 1 } rocs_dtype;
 
+/* Without an activation NaN stays NaN. Under ROCS_ACT_RELU a NaN becomes 0 or
+ * stays NaN (by its sign, in the bf16 kernels). */
 typedef enum rocs_activation { ROCS_ACT_NONE = 0, ROCS_ACT_RELU = 1 } rocs_activation;
 
 int32_t rocs_abi_version(void);

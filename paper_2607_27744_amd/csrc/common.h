@@ -42,6 +42,20 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   return __builtin_bit_cast(uint32_t, r);
 }
 
+// The activation of two packed bf16 values, the larger of each and of `lo` as
+// 16-bit integers: with act_floor(relu) = 0 the negative values (sign bit set)
+// are exactly those below zero and become +0, with the least integer every
+// value stays. So without an activation NaN stays NaN; under ReLU a NaN with
+// its sign set becomes 0 and any other stays. Written as the one instruction:
+// the compiler's own lowering of a packed max on a bit-cast pair has been seen
+// to drop the second word of the pair.
+__device__ __forceinline__ uint32_t act_floor(bool relu) { return relu ? 0u : 0x80008000u; }
+__device__ __forceinline__ uint32_t act_bf16x2(uint32_t p, uint32_t lo) {
+  uint32_t r;
+  asm("v_pk_max_i16 %0, %1, %2" : "=v"(r) : "v"(p), "s"(lo));
+  return r;
+}
+
 __device__ __forceinline__ float bf16_lo(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
 

@@ -173,7 +173,7 @@ void glm_fm_linear_bf16(const bf16_t* __restrict__ xr, const bf16_t* __restrict_
       for (int q = 0; q < KQ; ++q) asm volatile("" :: "v"(as_u32x4(wf[fm][q])));
   }
   if (nxt.live) wait_vmcnt<NX>(); else wait_vmcnt<0>();
-  const float lo = relu ? 0.f : -INFINITY;
+  const uint32_t lo = act_floor(relu);
   int buf = 0, par = 0;
   while (true) {
     ring_barrier();            // X^C, X^R, Zb of `cur` in; Y^C free
@@ -257,7 +257,7 @@ void glm_fm_linear_bf16(const bf16_t* __restrict__ xr, const bf16_t* __restrict_
 #pragma unroll
         for (int fm = 0; fm < FB; ++fm) acc[fm] = mfma32(wf[fm][q], y, acc[fm]);
       }
-      // Activation, bf16, stores. fl_swap leaves the lanes of one candidate
+      // bf16, activation, stores. fl_swap leaves the lanes of one candidate
       // with 16-byte pieces 32 bytes apart; exchanging 16-lane rows between
       // the two pieces puts four lanes on 64 contiguous bytes (1 us less at
       // 65,536 candidates). Store i takes candidates 16 i .. + 15, and is
@@ -265,13 +265,12 @@ void glm_fm_linear_bf16(const bf16_t* __restrict__ xr, const bf16_t* __restrict_
       bf16_t* op = out + (int64_t)(cur.n0 + c16) * D + fw + 16 * (q4 & 1) + 8 * h2;
 #pragma unroll
       for (int fm = 0; fm < FB; ++fm) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[fm][e] = fmaxf(acc[fm][e], lo);
         const u32x4 s0 = fl_swap(acc[fm], 0), s1 = fl_swap(acc[fm], 1);
         u32x4 o[2];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const auto t = __builtin_amdgcn_permlane16_swap(s0[e], s1[e], false, false);
+          const auto t = __builtin_amdgcn_permlane16_swap(act_bf16x2(s0[e], lo),
+                                                          act_bf16x2(s1[e], lo), false, false);
           o[0][e] = t[0];
           o[1][e] = t[1];
         }

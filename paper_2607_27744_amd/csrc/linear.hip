@@ -127,17 +127,6 @@ __global__ __launch_bounds__(512) void request_gemm_bf16(
   }
 }
 
-// ReLU of two packed bf16 values: as 16-bit integers the negative values
-// (sign bit set) are exactly those below zero, so a packed integer max with
-// zero clamps them (and -0) to +0. Written as the one instruction: the
-// compiler's own lowering of a packed max on a bit-cast pair has been seen
-// to drop the second word of the pair.
-__device__ __forceinline__ uint32_t relu_bf16x2(uint32_t p) {
-  uint32_t r;
-  asm("v_pk_max_i16 %0, %1, 0" : "=v"(r) : "v"(p));
-  return r;
-}
-
 // ---------------------------------------------------------------------------
 // Tiled candidate GEMM, bf16 MFMA 32x32x16: any map, any K and D of the fast
 // path (multiples of 8 and 4), the pointwise residual input, and calls too
@@ -325,6 +314,7 @@ void ikbo_gemm_tile(
   const uint32_t st = (uint32_t)(wave * 32 * ORB);
   const int64_t nw = n0 + wn0;
   const int dw = m0 + wm0;
+  const uint32_t lo = act_floor(relu);
 #pragma unroll
   for (int fn = 0; fn < FN; ++fn) {
     if constexpr (ZLATE) load_z(fn);
@@ -340,10 +330,8 @@ void ikbo_gemm_tile(
           const int e = 4 * (2 * j + u);
           p[u][0] = pack_bf16x2(a[e] + zq[0], a[e + 1] + zq[1]);
           p[u][1] = pack_bf16x2(a[e + 2] + zq[2], a[e + 3] + zq[3]);
-          if (relu) {
-            p[u][0] = relu_bf16x2(p[u][0]);
-            p[u][1] = relu_bf16x2(p[u][1]);
-          }
+          p[u][0] = act_bf16x2(p[u][0], lo);
+          p[u][1] = act_bf16x2(p[u][1], lo);
         }
         const auto s0 = __builtin_amdgcn_permlane32_swap(p[0][0], p[1][0], false, false);
         const auto s1 = __builtin_amdgcn_permlane32_swap(p[0][1], p[1][1], false, false);
@@ -780,8 +768,8 @@ void ikbo_gemm_stream(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w
     lo = pack_bf16x2(v0, v1);
     hi = pack_bf16x2(v2, v3);
     if constexpr (RELU) {
-      lo = relu_bf16x2(lo);
-      hi = relu_bf16x2(hi);
+      lo = act_bf16x2(lo, 0u);
+      hi = act_bf16x2(hi, 0u);
     }
   };
   auto swapped = [&](int fm, int fn, int j) __attribute__((always_inline)) {

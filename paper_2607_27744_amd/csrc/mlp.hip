@@ -64,12 +64,11 @@ __device__ __forceinline__ int mlp_swizzle(int row) {
 }
 
 // Four fp32 accumulator values of one lane (units u .. u + 3 of one
-// candidate) plus an additive row, then max with `lo` (0 for ReLU, -inf for
-// none: no branch), as two packed bf16 pairs.
-__device__ __forceinline__ void pack4(const f32x16& acc, int q, f32x4 add, float lo,
-                                      uint32_t& p0, uint32_t& p1) {
-  p0 = pack_bf16x2(fmaxf(acc[4 * q] + add[0], lo), fmaxf(acc[4 * q + 1] + add[1], lo));
-  p1 = pack_bf16x2(fmaxf(acc[4 * q + 2] + add[2], lo), fmaxf(acc[4 * q + 3] + add[3], lo));
+// candidate) with their activation (act_floor), as two packed bf16 pairs.
+__device__ __forceinline__ void pack4(const f32x16& acc, int q, uint32_t lo, uint32_t& p0,
+                                      uint32_t& p1) {
+  p0 = act_bf16x2(pack_bf16x2(acc[4 * q], acc[4 * q + 1]), lo);
+  p1 = act_bf16x2(pack_bf16x2(acc[4 * q + 2], acc[4 * q + 3]), lo);
 }
 
 // Accumulator rows 8 q + 4 hh + i (q = 2 s, 2 s + 1) of one 32-unit block,
@@ -216,7 +215,7 @@ void ikbo_mlp2_bf16(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1,
   const uint32_t f2 = (uint32_t)(l32 * ROWB2 + 16 * (hh ^ mlp_swizzle<8>(l32)));
   const uint32_t fa2 = (uint32_t)(W2O + 32 * OBW * og * ROWB2) + f2;
   const uint32_t fh = (uint32_t)(HO + 64 * cg * ROWB2) + f2;
-  const float lo1 = relu1 ? 0.f : -INFINITY, lo2 = relu2 ? 0.f : -INFINITY;
+  const uint32_t lo1 = act_floor(relu1), lo2 = act_floor(relu2);
   const int nch = DH / HC;
   f32x16 acc2[OBW][2];
   // First product of the chunk in W1 slot `par`, on top of acc1; W1 fragments
@@ -241,9 +240,8 @@ void ikbo_mlp2_bf16(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1,
   // Activation, bf16, into H buffer `par`.
   auto put_h = [&](int par) __attribute__((always_inline)) {
     uint32_t p[4][2];
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) pack4(acc1, q, zero, lo1, p[q][0], p[q][1]);
+    for (int q = 0; q < 4; ++q) pack4(acc1, q, lo1, p[q][0], p[q][1]);
 #pragma unroll
     for (int s = 0; s < 2; ++s)
       *reinterpret_cast<ROCS_LDS u32x4*>(
@@ -336,9 +334,8 @@ void ikbo_mlp2_bf16(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1,
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         uint32_t p[4][2];
-        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) pack4(acc2[ob][j], q, zero, lo2, p[q][0], p[q][1]);
+        for (int q = 0; q < 4; ++q) pack4(acc2[ob][j], q, lo2, p[q][0], p[q][1]);
         const u32x4 s0 = swap_halves(p, 0), s1 = swap_halves(p, 1);
         u32x4 o[2];
 #pragma unroll
@@ -453,8 +450,7 @@ void ikbo_mlp2_small(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1
     if (u + 2 < units) issue(u + 2);
   };
 
-  const float lo1 = relu1 ? 0.f : -__builtin_inff();
-  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  const uint32_t lo1 = act_floor(relu1);
   int u = 0;
   for (int hb = wave; hb < blocks; hb += 8) {
     f32x16 acc = f32x16{};
@@ -474,7 +470,7 @@ void ikbo_mlp2_small(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1
     }
     uint32_t p[4][2];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) pack4(acc, q, zero, lo1, p[q][0], p[q][1]);
+    for (int q = 0; q < 4; ++q) pack4(acc, q, lo1, p[q][0], p[q][1]);
 #pragma unroll
     for (int j = 0; j < 2; ++j)
       *reinterpret_cast<u32x4*>(lds + l32 * stride + 2 * (32 * hb + 16 * j + 8 * hh)) =
@@ -519,10 +515,10 @@ void ikbo_mlp2_small(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w1
       for (int i = 0; i < 4; ++i) acc[4 * q + i] += v[i];
     }
   }
-  const float lo2 = relu2 ? 0.f : -__builtin_inff();
+  const uint32_t lo2 = act_floor(relu2);
   uint32_t p[4][2];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) pack4(acc, q, zero, lo2, p[q][0], p[q][1]);
+  for (int q = 0; q < 4; ++q) pack4(acc, q, lo2, p[q][0], p[q][1]);
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const u32x4 v = swap_halves(p, j);            // every lane takes part in the swap

@@ -144,3 +144,18 @@ def test_fused_block_walk_and_slices(gpu_lib, counts, d):
     n = c.n_cand
     rows = np.unique(np.concatenate([np.arange(0, n, max(1, n // 400)), c.cand_offsets[1:] - 1]))
     assert_close(got[rows], _want(c, rows=rows)[0], f"fm_linear N{n} d{d}")
+
+
+@pytest.mark.parametrize("shape", [(32, 8, 128, 64), (16, 4, 64, 48)], ids=["fused", "two operators"])
+@pytest.mark.parametrize("act", ["none", "relu"])
+def test_nan_stays_in_its_row_and_is_no_infinity(gpu_lib, shape, act):
+    f_req, f_cand, emb, d = shape
+    c = wl.fm_linear_case([70, 0, 33], f_req, f_cand, emb, d, seed=6)
+    want, _ = _run(c, act)
+    c.x_cand = c.x_cand.copy()
+    c.x_cand[4, 0, 0], c.x_cand[80, 1, 3] = np.nan, np.copysign(np.nan, -1)
+    got, _ = _run(c, act)
+    rows = np.setdiff1d(np.arange(103), [4, 80])
+    assert np.array_equal(got[rows], want[rows])
+    part = got[[4, 80]]
+    assert np.all(np.isnan(part) | (part == 0) if act == "relu" else np.isnan(part))

@@ -134,3 +134,30 @@ def test_few_candidates(gpu_lib, counts, k_cand, d_h, d_o):
     rows = np.unique(np.concatenate([np.arange(min(c.n_cand, 96)), [c.n_cand - 1],
                                      np.random.default_rng(1).integers(0, c.n_cand, 200)]))
     assert_close(got[rows], _want(c, act2="relu", rows=rows), f"{counts} {k_cand} {d_h} {d_o}")
+
+
+@pytest.mark.parametrize("n,k_cand", [(200, 128), (17000, 128), (200, 136)],
+                         ids=["small", "persistent", "two launches"])
+@pytest.mark.parametrize("acts", [("none", "none"), ("relu", "none"), ("relu", "relu")],
+                         ids="-".join)
+def test_nan_stays_in_its_row_and_is_no_infinity(gpu_lib, n, k_cand, acts):
+    # Every form of the operator: NaN of either sign stays NaN where there is no
+    # activation and becomes nothing but 0 under ReLU.
+    c = wl.mlp2_case([n - 60, 60], 16, k_cand, 64, 128, seed=5)
+    x, b2 = c.x_cand.copy(), c.b2.copy()
+    x[3, 0], x[n - 1, 5] = np.nan, np.copysign(np.nan, -1)
+    b2[7], b2[9] = np.nan, np.copysign(np.nan, -1)
+    args = dict(x_req=dev_bf16(c.x_req), w1_req=dev_bf16(c.w1_req), b1=dev_f32(c.b1),
+                cand_offsets=dev_i32(c.cand_offsets), activation1=acts[0], activation2=acts[1])
+    want = host(ops.ikbo_mlp2(dev_bf16(c.x_cand), dev_bf16(c.w1_cand), dev_bf16(c.w2),
+                              b2=dev_f32(c.b2), **args))
+    got = host(ops.ikbo_mlp2(dev_bf16(x), dev_bf16(c.w1_cand), dev_bf16(c.w2), b2=dev_f32(b2),
+                             **args))
+    rows, cols = np.setdiff1d(np.arange(n), [3, n - 1]), np.setdiff1d(np.arange(128), [7, 9])
+    assert np.array_equal(got[np.ix_(rows, cols)], want[np.ix_(rows, cols)])
+    spoiled = [got[rows][:, [7, 9]]]
+    if acts[0] == "none":                        # else the hidden layer's ReLU comes between
+        spoiled.append(got[[3, n - 1]])
+    assert not np.any(np.isinf(got))
+    for part in spoiled:
+        assert np.all(np.isnan(part) | (part == 0) if acts[1] == "relu" else np.isnan(part))
