@@ -43,8 +43,9 @@ __global__ __launch_bounds__(256) void request_ids_kernel(const int32_t* __restr
 // workgroups at batch size R is bound by the latency of a wave's loads: with
 // eight waves and eight steps in flight a K of 2048 is one round trip to L2
 // (16 requests, 1024 outputs: 7 us), where four waves with four steps in
-// flight made four (12 us); a K of 4096, 1024 outputs: 22 -> 12 us. Workgroups past the tiles expand the index map when the
-// candidate GEMM needs it.
+// flight made four (12 us); a K of 4096, 1024 outputs: 22 -> 12 us. Many
+// requests take a wave per tile (request_gemm_many). Workgroups past the tiles
+// expand the index map when the candidate GEMM needs it.
 // ---------------------------------------------------------------------------
 struct RequestOut {          // the optional Y^R part of the stacked weight
   const bf16_t* w;           // W_RR [d, K]
@@ -54,28 +55,58 @@ struct RequestOut {          // the optional Y^R part of the stacked weight
 };
 
 constexpr int kReqAhead = 8;   // k-steps of a wave in flight
-constexpr int kReqMaxBlocks = 1 << 22;   // workgroups of 512 per launch; they loop over more tiles
+constexpr int kReqMaxBlocks = 1 << 21;   // workgroups of 512 per launch; they loop over more tiles
+// ... beside the workgroups that expand a map of up to 2^31 - 1 candidates.
+static_assert((int64_t)kReqMaxBlocks * 512 + (int64_t(1) << 31) + 512 < int64_t(1) << 32, "grid");
 
-// One 16 x 16 output tile `tile` of the stacked request GEMM, by a 512-thread
-// workgroup; `red` is 8 KiB of LDS. Returns whether the tile was a Zb tile
-// (the candidate side's input) and, for wave 0, its (row block, column block).
+// One 16 x 16 output tile of the stacked request GEMM, as one wave sees it.
+struct RequestTile {
+  const bf16_t* x;           // this lane's eight k of its request row ...
+  const bf16_t* w;           // ... and of its weight row
+  const float* bias;
+  int r0, d0, D;             // first request, first column, columns of this output
+  bool to_y, rok, dok;       // a tile of Y^R; this lane's rows are inside
+
+  __device__ __forceinline__ RequestTile(const bf16_t* x_in, const bf16_t* w_in,
+                                         const float* bias_in, int R, int K, int D_in, int tiles_d,
+                                         const RequestOut& yr, int tile, int lane) {
+    const int tiles_all = yr.tiles + tiles_d;
+    const int t = tile % tiles_all;
+    to_y = t < yr.tiles;                          // a column tile of Y^R
+    bias = to_y ? yr.bias : bias_in;
+    D = to_y ? yr.d : D_in;
+    r0 = (tile / tiles_all) * 16;
+    d0 = (to_y ? t : t - yr.tiles) * 16;
+    const int row = lane & 15, kq = (lane >> 4) * 8;
+    dok = d0 + row < D;
+    rok = r0 + row < R;
+    w = (to_y ? yr.w : w_in) + (int64_t)(d0 + row) * K + kq;
+    x = x_in + (int64_t)(r0 + row) * K + kq;
+  }
+  // s[i] = Z[r0 + lane % 16][d0 + 4 (lane / 16) + i] without the bias.
+  __device__ __forceinline__ void store(f32x4 s, float* z, const RequestOut& yr, int lane) const {
+    const int row = lane & 15, d = d0 + (lane >> 4) * 4;
+    if (!rok || d >= D) return;
+    if (bias != nullptr) s += *reinterpret_cast<const f32x4*>(bias + d);
+    if (to_y) {
+      if (yr.relu) s = f32x4{fmaxf(s[0], 0.f), fmaxf(s[1], 0.f), fmaxf(s[2], 0.f), fmaxf(s[3], 0.f)};
+      *reinterpret_cast<u32x2*>(yr.y + (int64_t)(r0 + row) * D + d) =
+          u32x2{pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3])};
+    } else {
+      *reinterpret_cast<f32x4*>(z + (int64_t)(r0 + row) * D + d) = s;
+    }
+  }
+};
+
+// Tile `tile` by a 512-thread workgroup; `red` is 8 KiB of LDS. Returns whether
+// it was a Zb tile (the candidate side's input); wave 0 has stored it.
 __device__ __forceinline__ bool request_tile(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w_in,
     const float* __restrict__ bias_in, float* __restrict__ z, int R, int K, int D_in,
     int tiles_d, const RequestOut& yr, int tile, ROCS_LDS f32x4* red) {
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int tiles_all = yr.tiles + tiles_d;
-  const int t = tile % tiles_all;
-  const bool to_y = t < yr.tiles;                 // a column tile of Y^R
-  const bf16_t* w = to_y ? yr.w : w_in;
-  const float* bias = to_y ? yr.bias : bias_in;
-  const int D = to_y ? yr.d : D_in;
-  const int r0 = (tile / tiles_all) * 16, d0 = (to_y ? t : t - yr.tiles) * 16;
-  const int row = lane & 15, kq = (lane >> 4) * 8;
-  const bool dok = d0 + row < D, rok = r0 + row < R;
-  const bf16_t* wp = w + (int64_t)(d0 + row) * K + kq;
-  const bf16_t* xp = x + (int64_t)(r0 + row) * K + kq;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const RequestTile t(x, w_in, bias_in, R, K, D_in, tiles_d, yr, tile, lane);
+  const int kq = (lane >> 4) * 8;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   for (int k0 = wave * 32; k0 < K; k0 += 256 * kReqAhead) {
     u32x4 a[kReqAhead], b[kReqAhead];
@@ -83,11 +114,11 @@ __device__ __forceinline__ bool request_tile(
     for (int j = 0; j < kReqAhead; ++j) {
       const int k = k0 + 256 * j;
       const bool kok = k + kq < K;
-      a[j] = load16(wp + k, dok && kok);
-      b[j] = load16(xp + k, rok && kok);
+      a[j] = load16(t.w + k, t.dok && kok);
+      b[j] = load16(t.x + k, t.rok && kok);
     }
 #pragma unroll
-    for (int j = 0; j < kReqAhead; ++j)   // acc[i] = Z[r0 + row][d0 + 4 (lane / 16) + i]
+    for (int j = 0; j < kReqAhead; ++j)
       if (k0 + 256 * j < K) acc = mfma16(as_bf16x8(a[j]), as_bf16x8(b[j]), acc);
   }
   red[wave * kWave + lane] = acc;
@@ -96,19 +127,9 @@ __device__ __forceinline__ bool request_tile(
     f32x4 s = red[lane];
 #pragma unroll
     for (int w = 1; w < 8; ++w) s += red[w * kWave + lane];
-    const int d = d0 + (lane >> 4) * 4;
-    if (rok && d < D) {
-      if (bias != nullptr) s += *reinterpret_cast<const f32x4*>(bias + d);
-      if (to_y) {
-        if (yr.relu) s = f32x4{fmaxf(s[0], 0.f), fmaxf(s[1], 0.f), fmaxf(s[2], 0.f), fmaxf(s[3], 0.f)};
-        *reinterpret_cast<u32x2*>(yr.y + (int64_t)(r0 + row) * D + d) =
-            u32x2{pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3])};
-      } else {
-        *reinterpret_cast<f32x4*>(z + (int64_t)(r0 + row) * D + d) = s;
-      }
-    }
+    t.store(s, z, yr, lane);
   }
-  return !to_y;
+  return !t.to_y;
 }
 
 __global__ __launch_bounds__(512) void request_gemm_bf16(
@@ -125,6 +146,67 @@ __global__ __launch_bounds__(512) void request_gemm_bf16(
     request_tile(x, w_in, bias_in, z, R, K, D_in, tiles_d, yr, t, (ROCS_LDS f32x4*)red);
     __syncthreads();                      // red is free for the next tile
   }
+}
+
+// The same tiles, a wave each: the eight slices of K in eight accumulators,
+// added in the same order, so the values are the same. For many requests: the
+// tiles fill the chip by themselves, and at a short K a workgroup per tile has
+// most of its waves without a k-step.
+__global__ __launch_bounds__(512) void request_gemm_many(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ w_in, const float* __restrict__ bias_in,
+    float* __restrict__ z, const int32_t* __restrict__ off, int32_t* __restrict__ ids, int R,
+    int64_t N, int K, int D_in, int tiles_d, int z_tiles, int z_blocks, RequestOut yr) {
+  if ((int)blockIdx.x >= z_blocks) {
+    const int64_t n = (int64_t)(blockIdx.x - z_blocks) * 512 + threadIdx.x;
+    if (n < N) ids[n] = owner_of(off, R, n);
+    return;
+  }
+  const int lane = threadIdx.x & 63, kq = (lane >> 4) * 8;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int64_t at = (int64_t)blockIdx.x * 8 + wave; at < z_tiles; at += (int64_t)z_blocks * 8) {
+    const RequestTile t(x, w_in, bias_in, R, K, D_in, tiles_d, yr, (int)at, lane);
+    f32x4 acc[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < K; k0 += 256) {
+      u32x4 a[8], b[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const bool kok = k0 + 32 * j + kq < K;
+        a[j] = load16(t.w + k0 + 32 * j, t.dok && kok);
+        b[j] = load16(t.x + k0 + 32 * j, t.rok && kok);
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (k0 + 32 * j < K) acc[j] = mfma16(as_bf16x8(a[j]), as_bf16x8(b[j]), acc[j]);
+    }
+    f32x4 s = acc[0];
+#pragma unroll
+    for (int j = 1; j < 8; ++j) s += acc[j];
+    t.store(s, z, yr, lane);
+  }
+}
+
+// Launch of the request GEMM with `ids` expanded beside it (n_ids candidates).
+hipError_t launch_request(const LinearArgs& a, int tiles_d, int req_tiles, int64_t n_ids,
+                          const RequestOut& yr, hipStream_t s) {
+  // A wave per tile from eight tiles a CU on, more the longer its K is: a wave
+  // walks K alone. Whole call (us, workgroup / wave per tile), requests x
+  // outputs, K: 256 x 1024 (1,024 tiles), 256: 9.0 / 9.5, K 1024: 13.8 / 19.9;
+  // 512 x 1024 (2,048), 64: 11.6 / 7.9, K 1024: 22.2 / 20.4; 300 x 2000 (2,375),
+  // 2000: 81 / 93; 2000 x 1024 (8,000), 4096: 232 / 232; 16,384 x 1024 (65,536),
+  // 64: 207 / 67, K 256: 235 / 138.
+  int cus = 0;
+  const hipError_t ce = current_cu_count(&cus);
+  if (ce != hipSuccess) return ce;
+  const bool many = (int64_t)req_tiles * 1024 >= 8 * (int64_t)cus * (a.k_req > 1024 ? a.k_req : 1024);
+  const int blocks = many ? (req_tiles + 7) / 8 : req_tiles;
+  const int z_blocks = blocks < kReqMaxBlocks ? blocks : kReqMaxBlocks;
+  const int id_blocks = (int)((n_ids + 511) / 512);
+  return launch_kernel(many ? request_gemm_many : request_gemm_bf16, dim3(z_blocks + id_blocks),
+                       dim3(512), s, static_cast<const bf16_t*>(a.x_req),
+                       static_cast<const bf16_t*>(a.w_req), a.bias, a.z, a.cand_offsets, a.ids,
+                       (int)a.R, a.N, (int)a.k_req, (int)a.d_out, tiles_d, req_tiles, z_blocks, yr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1097,12 +1179,8 @@ hipError_t launch_request_table(const LinearArgs& a, hipStream_t s) {
   const int tiles_d = (int)((a.d_out + 15) / 16);
   if (!grid_fits((int64_t)tiles_d * ((a.R + 15) / 16), 256)) return hipErrorInvalidConfiguration;
   const int req_tiles = tiles_d * (int)((a.R + 15) / 16);
-  const int z_blocks = req_tiles < kReqMaxBlocks ? req_tiles : kReqMaxBlocks;
   const RequestOut none{nullptr, nullptr, nullptr, 0, 0, 0};
-  return launch_kernel(request_gemm_bf16, dim3(z_blocks), dim3(512), s,
-                       static_cast<const bf16_t*>(a.x_req), static_cast<const bf16_t*>(a.w_req),
-                       a.bias, a.z, a.cand_offsets, a.ids, (int)a.R, a.N, (int)a.k_req,
-                       (int)a.d_out, tiles_d, req_tiles, z_blocks, none);
+  return launch_request(a, tiles_d, req_tiles, 0, none, s);
 }
 
 hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
@@ -1160,13 +1238,7 @@ hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
     return hipErrorInvalidConfiguration;
   const int req_tiles = (yr.tiles + tiles_d) * (int)((a.R + 15) / 16);
   if (a.k_req > 0 && !fused) {
-    const int id_blocks = stream || a.ids_given ? 0 : (int)((a.N + 511) / 512);
-    const int z_blocks = req_tiles < kReqMaxBlocks ? req_tiles : kReqMaxBlocks;
-    hipError_t e = launch_kernel(request_gemm_bf16, dim3(z_blocks + id_blocks), dim3(512), s,
-                                 static_cast<const bf16_t*>(a.x_req),
-                                 static_cast<const bf16_t*>(a.w_req), a.bias, a.z,
-                                 a.cand_offsets, a.ids, (int)a.R, a.N, (int)a.k_req,
-                                 (int)a.d_out, tiles_d, req_tiles, z_blocks, yr);
+    const hipError_t e = launch_request(a, tiles_d, req_tiles, stream || a.ids_given ? 0 : a.N, yr, s);
     if (e != hipSuccess) return e;
   }
   if (a.N == 0) return hipSuccess;      // request-side output only

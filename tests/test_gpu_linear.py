@@ -279,3 +279,27 @@ def test_combined_request_candidate_kernel(gpu_lib, shape):
     y_r, y_c = ops.ikbo_linear_combined(x_req, x_cand, w_cr, w_cc, off, workspace=ws, **kw)
     assert y_r is None
     np.testing.assert_array_equal(host(y_c), host(sep_c))
+
+
+@pytest.mark.parametrize("k_req", [8, 72, 520])
+def test_many_requests(gpu_lib, k_req):
+    # 66 x 34 tiles of 16 x 16 on the request side: a wave takes a tile, where
+    # the combined call keeps a workgroup per tile. The same sums in the same
+    # order; the last rows and columns are partial, K ends inside a slice of 256.
+    rng = np.random.default_rng(k_req)
+    case = wl.linear_case(rng.integers(0, 4, 1041), k_req, 64, 508, seed=k_req, bias_std=0.2)
+    w_rr = round_bf16(rng.standard_normal((20, k_req)) * k_req ** -0.5)
+    b_rr = rng.standard_normal(20)
+    args = (dev_bf16(case.x_req), dev_bf16(case.x_cand))
+    w_cr, w_cc, off = dev_bf16(case.w_req), dev_bf16(case.w_cand), dev_i32(case.cand_offsets)
+    kw = dict(w_rr=dev_bf16(w_rr), b_req=dev_f32(b_rr), b_cand=dev_f32(case.bias),
+              activation="relu")
+    same_r, same_c = ops.ikbo_linear_combined(*args, w_cr, w_cc, off, **kw)
+    w = kw.pop("w_rr")
+    y_req, y_cand = ops.glm_linear(*args, w, w_cr, w_cc, off, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(y_req, same_r) and torch.equal(y_cand, same_c)
+    want_r, want_c = ikbo.glm_linear(case.x_req, case.x_cand, w_rr, case.w_req, case.w_cand, b_rr,
+                                     case.bias, case.cand_offsets, "relu")
+    assert_close(host(y_req), round_bf16(want_r), "y_req")
+    assert_close(host(y_cand), round_bf16(want_c), "y_cand")
