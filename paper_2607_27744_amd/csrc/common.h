@@ -49,6 +49,11 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 // its sign set becomes 0 and any other stays. Written as the one instruction:
 // the compiler's own lowering of a packed max on a bit-cast pair has been seen
 // to drop the second word of the pair.
+__device__ __forceinline__ uint32_t relu_bf16x2(uint32_t p) {
+  uint32_t r;
+  asm("v_pk_max_i16 %0, %1, 0" : "=v"(r) : "v"(p));
+  return r;
+}
 __device__ __forceinline__ uint32_t act_floor(bool relu) { return relu ? 0u : 0x80008000u; }
 __device__ __forceinline__ uint32_t act_bf16x2(uint32_t p, uint32_t lo) {
   uint32_t r;

@@ -15,6 +15,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "launch.h"
+#include "linear_rule.h"
 
 #include <atomic>
 #include <random>
@@ -188,17 +189,14 @@ __global__ __launch_bounds__(512) void request_gemm_many(
 }
 
 // Launch of the request GEMM with `ids` expanded beside it (n_ids candidates).
-hipError_t launch_request(const LinearArgs& a, int tiles_d, int req_tiles, int64_t n_ids,
-                          const RequestOut& yr, hipStream_t s) {
+hipError_t launch_request(const LinearArgs& a, int cus, int tiles_d, int req_tiles,
+                          int64_t n_ids, const RequestOut& yr, hipStream_t s) {
   // A wave per tile from eight tiles a CU on, more the longer its K is: a wave
   // walks K alone. Whole call (us, workgroup / wave per tile), requests x
   // outputs, K: 256 x 1024 (1,024 tiles), 256: 9.0 / 9.5, K 1024: 13.8 / 19.9;
   // 512 x 1024 (2,048), 64: 11.6 / 7.9, K 1024: 22.2 / 20.4; 300 x 2000 (2,375),
   // 2000: 81 / 93; 2000 x 1024 (8,000), 4096: 232 / 232; 16,384 x 1024 (65,536),
   // 64: 207 / 67, K 256: 235 / 138.
-  int cus = 0;
-  const hipError_t ce = current_cu_count(&cus);
-  if (ce != hipSuccess) return ce;
   const bool many = (int64_t)req_tiles * 1024 >= 8 * (int64_t)cus * (a.k_req > 1024 ? a.k_req : 1024);
   const int blocks = many ? (req_tiles + 7) / 8 : req_tiles;
   const int z_blocks = blocks < kReqMaxBlocks ? blocks : kReqMaxBlocks;
@@ -491,7 +489,7 @@ void ikbo_gemm_tile(
 //
 // Rows past the tile's end are clamped loads whose results are not stored.
 // ---------------------------------------------------------------------------
-constexpr int kStreamBM = 256, kStreamBN = 256, kStreamBK = 64;
+constexpr int kStreamBK = 64;
 constexpr int kCpolNT = 2;   // buffer-instruction cache policy bits: NT (the former SLC bit)
 
 struct StreamTile {
@@ -850,8 +848,8 @@ void ikbo_gemm_stream(const bf16_t* __restrict__ x, const bf16_t* __restrict__ w
     lo = pack_bf16x2(v0, v1);
     hi = pack_bf16x2(v2, v3);
     if constexpr (RELU) {
-      lo = act_bf16x2(lo, 0u);
-      hi = act_bf16x2(hi, 0u);
+      lo = relu_bf16x2(lo);
+      hi = relu_bf16x2(hi);
     }
   };
   auto swapped = [&](int fm, int fn, int j) __attribute__((always_inline)) {
@@ -1180,7 +1178,10 @@ hipError_t launch_request_table(const LinearArgs& a, hipStream_t s) {
   if (!grid_fits((int64_t)tiles_d * ((a.R + 15) / 16), 256)) return hipErrorInvalidConfiguration;
   const int req_tiles = tiles_d * (int)((a.R + 15) / 16);
   const RequestOut none{nullptr, nullptr, nullptr, 0, 0, 0};
-  return launch_request(a, tiles_d, req_tiles, 0, none, s);
+  int cus = 0;
+  const hipError_t e = current_cu_count(&cus);
+  if (e != hipSuccess) return e;
+  return launch_request(a, cus, tiles_d, req_tiles, 0, none, s);
 }
 
 hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
@@ -1204,7 +1205,7 @@ hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
   const hipError_t ce = current_cu_count(&cus);
   if (ce != hipSuccess) return ce;
   const int64_t tiles_m256 = (a.d_out + kStreamBM - 1) / kStreamBM;
-  const int64_t slots = (a.k_req > 0 ? a.R : 0) + (a.N + kStreamBN - 1) / kStreamBN;
+  const int64_t slots = stream_slots(a.N, a.k_req > 0 ? a.R : 0);
   const bool can_stream = !a.ids_given && a.x_cand_add == nullptr && a.k_cand % kStreamBK == 0 &&
                       a.k_cand < (int64_t(1) << 22) && a.d_out < (int64_t(1) << 22) &&
                       slots * tiles_m256 < (int64_t(1) << 31);
@@ -1214,21 +1215,8 @@ hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
   // the combined kernel needs (an L2 write-back per request tile, an L2
   // invalidate per workgroup) costs more than the launch it saves.
   const bool fused = a.combined && can_stream && a.k_req > 0 && a.N > 0;
-  // The streaming kernel's workgroups, one per CU, take whole 256 x 256 tiles,
-  // so its time is that of its last round; the tiled kernel's smaller tiles
-  // pack better but stream K more slowly, the more so the longer K is.
-  // Measured (us, streaming / tiled, with the share of the rounds' area that
-  // the call fills): K 256: 0.65, 64,324 x 512: 45 / 35; 0.76, 100,000 x 512:
-  // 50 / 51, 200,000 x 256: 60 / 53; 1, 163,840 x 1024: 107 / 158. K 512 and
-  // more: 0.25, 8,192 x 512: 54 / 37; 0.51, 50,000 x 512: 60 / 48; 0.67, 8,192
-  // x 8,192: 92 / 117; 0.72, 48,000 x 512: 37 / 38; 0.76, 100,000 x 1024: 135
-  // / 172; 1, 32,768 x 1024: 36 / 45.
-  // (Only for calls that can stream: their sizes keep the products in 64 bits.)
-  auto fills = [&]() {
-    const int64_t area = ((slots * tiles_m256 + cus - 1) / cus) * cus * kStreamBM * kStreamBN;
-    return a.k_cand < 512 ? 4 * a.N * a.d_out >= 3 * area : 3 * a.N * a.d_out >= 2 * area;
-  };
-  const bool stream = can_stream && (fused || fills());
+  const bool stream = can_stream &&
+                      (fused || stream_pays(a.N, a.d_out, a.k_cand, a.k_req > 0 ? a.R : 0, cus));
   RequestOut yr{static_cast<const bf16_t*>(a.w_rr), a.b_rr, static_cast<bf16_t*>(a.y_req),
                 (int)a.d_req, a.y_req != nullptr ? (int)((a.d_req + 15) / 16) : 0, (int)a.relu};
   // No candidates: only the Y^R tiles (the request table has no reader).
@@ -1238,7 +1226,8 @@ hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
     return hipErrorInvalidConfiguration;
   const int req_tiles = (yr.tiles + tiles_d) * (int)((a.R + 15) / 16);
   if (a.k_req > 0 && !fused) {
-    const hipError_t e = launch_request(a, tiles_d, req_tiles, stream || a.ids_given ? 0 : a.N, yr, s);
+    const hipError_t e = launch_request(a, cus, tiles_d, req_tiles,
+                                        stream || a.ids_given ? 0 : a.N, yr, s);
     if (e != hipSuccess) return e;
   }
   if (a.N == 0) return hipSuccess;      // request-side output only

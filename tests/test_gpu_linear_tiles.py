@@ -69,11 +69,12 @@ def test_same_values_as_the_streaming_kernel(gpu_lib, counts, kc, d, act):
     assert torch.equal(got.view(torch.int16), stream.view(torch.int16))
 
 
-@pytest.mark.parametrize("kc", [448, 512], ids=["tiled", "streaming"])
-def test_rule_for_long_k(gpu_lib, kc):
-    # 2,900 x 4,096 fills 0.71 of one round of 256 x 256 tiles on 256 CUs:
-    # between the two shares of the rounds' area that decide below and from K 512.
-    c = wl.linear_case([1500, 0, 1399, 1], 24, kc, 4096, seed=kc, bias_std=0.2)
+@pytest.mark.parametrize("kc", [448, 512])
+@pytest.mark.parametrize("last", [1047, 1049], ids=["tiled", "streaming"])
+def test_both_sides_of_half_a_round(gpu_lib, kc, last):
+    # 2,048 and 2,050 x 4,096: half of one round of 256 x 256 tiles on 256 CUs
+    # and just more. (tests/test_linear_rule.py: which kernel that takes.)
+    c = wl.linear_case([1000, 0, last, 1], 24, kc, 4096, seed=kc, bias_std=0.2)
     args = (dev_bf16(c.x_req), dev_bf16(c.x_cand), dev_bf16(c.w_req), dev_bf16(c.w_cand),
             dev_i32(c.cand_offsets))
     _, stream = gpu_lib.ikbo_linear_combined(*args, b_cand=dev_f32(c.bias), activation="relu")
@@ -81,7 +82,7 @@ def test_rule_for_long_k(gpu_lib, kc):
                               cand_offsets=args[4], bias=dev_f32(c.bias), activation="relu")
     torch.cuda.synchronize()
     assert torch.equal(got.view(torch.int16), stream.view(torch.int16))
-    rows = np.array([0, 255, 256, 1499, 1500, 2047, 2898, 2899])
+    rows = np.array([0, 255, 256, 999, 1000, 2046, last + 999, last + 1000])
     want = ikbo.ikbo_linear(c.x_req, c.x_cand[rows], c.w_req, c.w_cand, c.bias, None, "relu",
                             request_map=ikbo.request_ids(c.cand_offsets)[rows])
     assert_close(host(got)[rows], round_bf16(want), f"k{kc}")
