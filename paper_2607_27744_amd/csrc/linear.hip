@@ -214,16 +214,19 @@ hipError_t launch_request(const LinearArgs& a, int cus, int tiles_d, int req_til
 //
 // Matrix-core roles: A = W_CC rows (output features d), B = candidate rows, so
 // each lane's accumulator holds, for one candidate, four runs of 4 consecutive
-// output features. Workgroup tile BM (features) x BN (candidates), 2 x 2
-// waves; two workgroups share a CU, so one's prologue (index map, request
-// rows, first slabs) and epilogue run under the other's products. K arrives in
+// output features. Workgroup tile BM (features) x BN (candidates), four waves,
+// WVM of them along the features; three workgroups share a CU (two of 64 x 64
+// with a residual), so one's prologue (index map, request rows, first slabs)
+// and epilogue run under the others' products. K arrives in
 // BK-wide slabs by LDS DMA, S - 1 slabs ahead of use; 16-byte chunks are
 // XOR-swizzled by row so that the 16 rows of a quarter-wave read fall on
 // distinct banks. Chunks past K come from a zeroed address, rows past the
 // operands repeat the last one and are not stored.
 //
 // HAS_ADD: the residual's slab travels the same way, and the sum round(x +
-// x_add) is formed on the fragments.
+// x_add) is formed on the fragments, by every wave along the features again:
+// about as much vector work as a pair of matrix instructions takes, so at a
+// longer K the waves stand side by side along the candidates (WVM 1).
 //
 // Epilogue: each candidate's own request row Z[m_n] (or the bias), loaded in
 // the prologue, is added after the products (the order of the streaming
@@ -236,18 +239,18 @@ hipError_t launch_request(const LinearArgs& a, int cus, int tiles_d, int req_til
 // within 5% (the residual form gains 10% from the epilogue: 100,000 x 1024,
 // K 512: 228 / 252 us). Against register-staged slabs with one slab ahead and
 // 8-byte stores: 64,324 x 512, K 256, shuffled: 58 -> 39 us; 407,816 x 552, K
-// 104: 310 -> 241; with residual 100,000 x 1024, K 512: 265 -> 228, 20,011 x
-// 300, K 360: 27 -> 22.5.
+// 104: 310 -> 241; with residual 100,000 x 1024, K 512: 227 -> 205, K 1024: 387
+// -> 385, 3,000 x 4096, K 4096: 189 -> 193, 20,011 x 300, K 360: 20.7 -> 19.5.
 // ---------------------------------------------------------------------------
 __device__ __constant__ u32x4 g_zero_chunk = {0u, 0u, 0u, 0u};
 
-template <int BM, int BN, int BK, int S, bool HAS_ADD>
+template <int BM, int BN, int BK, int S, bool HAS_ADD, int WVM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void ikbo_gemm_tile(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ xadd, const bf16_t* __restrict__ w,
     const float* __restrict__ z, const int32_t* __restrict__ ids, bf16_t* __restrict__ out,
     int64_t N, int K, int D, int tiles_m, int relu, int R) {
-  constexpr int WM = BM / 2, WN = BN / 2;      // wave block
+  constexpr int WM = BM / WVM, WN = BN / (4 / WVM);   // wave block
   constexpr int FM = WM / 32, FN = WN / 32;
   constexpr bool ZLATE = HAS_ADD;              // request rows loaded in the epilogue
   constexpr int ZFN = ZLATE ? 1 : FN;
@@ -269,7 +272,7 @@ void ikbo_gemm_tile(
   const uint32_t tile = xcd_remap(blockIdx.x, gridDim.x);
   const int m0 = (int)(tile % (uint32_t)tiles_m) * BM;
   const int64_t n0 = (int64_t)(tile / (uint32_t)tiles_m) * BN;
-  const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
+  const int wm0 = wave % WVM * WM, wn0 = wave / WVM * WN;
   const uint32_t lbase = lds_addr(lds);
   auto swz = [](int row) { return CPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; };
 
@@ -1114,12 +1117,12 @@ hipError_t launch_general(GeneralArgs<T> g, hipStream_t s) {
   return vec ? go(linear_general<T, 32, true, OUTF, EXT>) : go(linear_general<T, 32, false, OUTF, EXT>);
 }
 
-template <int BM, int BN, int BK, int S, bool HAS_ADD>
+template <int BM, int BN, int BK, int S, bool HAS_ADD, int WVM = 2>
 hipError_t launch_tile(const LinearArgs& a, hipStream_t s) {
   const int tiles_m = (int)((a.d_out + BM - 1) / BM);
   const int64_t grid = tiles_m * ((a.N + BN - 1) / BN);
   if (!grid_fits(grid, 256)) return hipErrorInvalidConfiguration;
-  return launch_kernel(ikbo_gemm_tile<BM, BN, BK, S, HAS_ADD>, dim3((uint32_t)grid), dim3(256), s,
+  return launch_kernel(ikbo_gemm_tile<BM, BN, BK, S, HAS_ADD, WVM>, dim3((uint32_t)grid), dim3(256), s,
                        static_cast<const bf16_t*>(a.x_cand),
                        static_cast<const bf16_t*>(a.x_cand_add),
                        static_cast<const bf16_t*>(a.w_cand), a.k_req > 0 ? a.z : a.bias,
@@ -1269,8 +1272,15 @@ hipError_t launch_linear(const LinearArgs& a, bool fast, hipStream_t s) {
   // (613 x 1024, K 256: 3.7 against 6.0 us; 2,000 x 1024, K 512: 10.3 / 12.9;
   // 8,192 x 512, K 2048, 256 tiles: 41.5 / 37.8).
   const bool small = ((a.d_out + 127) / 128) * ((a.N + 127) / 128) < cus;
-  if (a.x_cand_add != nullptr)
-    return small ? launch_tile<64, 64, 64, 3, true>(a, s) : launch_tile<128, 128, 32, 2, true>(a, s);
+  // Residual: four waves side by side along the candidates form each sum once,
+  // two by two waves twice. Two by two / side by side, us: 200,000 x 256, K 64:
+  // 27.5 / 28.6; 50,000 x 512, K 256: 32.3 / 31.1; 100,000 x 1024, K 512: 216 /
+  // 205; 8,000 x 1024, K 4096: 119 / 109.
+  if (a.x_cand_add != nullptr) {
+    if (small) return launch_tile<64, 64, 64, 3, true>(a, s);
+    return a.k_cand >= 256 ? launch_tile<128, 128, 32, 2, true, 1>(a, s)
+                           : launch_tile<128, 128, 32, 2, true>(a, s);
+  }
   return small ? launch_tile<64, 64, 64, 3, false>(a, s) : launch_tile<128, 128, 32, 3, false>(a, s);
 }
 
