@@ -305,24 +305,29 @@ hipError_t dispatch_nk(const LcbArgs& a, hipStream_t s) {
 // Request side, bf16 with E a multiple of 4: each thread makes 4 adjacent
 // embedding columns of NO stacked output rows (an 8-byte input load feeds 4 NO
 // products). At batch size R the kernel is bound by its loads' latency and
-// count: the four waves of a workgroup split the fields, up to 16 rows in
-// flight each, and reduce through LDS in a fixed order. VECW: four fields of a
+// count: with WF = 4 the four waves of a workgroup split the fields, up to 16
+// rows in flight each, and reduce through LDS in a fixed order; with WF = 1 (few
+// fields) each wave has outputs of its own: 8,000 candidates of 4,000 requests,
+// 16 fields, 64 rows x 128: 147 -> 69 us. VECW: four fields of a
 // weight row per load (F_r a multiple of 4, rows 8-byte aligned). Request plus
 // candidate side, one row with single weight loads / as chosen now: 65,536
 // candidates of 16 requests, 128 fields: 225 / 223.3 us; 8,000 of 22, 121
 // fields: 55.7 / 53.8; 1,500 of 3, 64 fields: 14.3 / 13.6 us.
-template <int NO, bool VECW>
+template <int NO, bool VECW, int WF>
 __global__ __launch_bounds__(256) void lcb_request_bf16x4(
     const bf16_t* __restrict__ xr, const bf16_t* __restrict__ wrr, const bf16_t* __restrict__ wcr,
     bf16_t* __restrict__ yr, float* __restrict__ z, int R, int FR, int OR, int OC, int E) {
   constexpr int AHEAD = VECW || NO > 1 ? 16 : 8;
-  __shared__ f32x4 part[4][NO][kWave];
+  __shared__ f32x4 part[WF][NO][kWave];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int E4 = E / 4, O = OR + OC;
   const int64_t per_req = (int64_t)((O + NO - 1) / NO) * E4, total = R * per_req;
   const int per_wave = (FR + 15) / 16 * 4;
-  const int f0 = min(wave * per_wave, FR), f1 = min(f0 + per_wave, FR);
-  for (int64_t base = (int64_t)blockIdx.x * kWave; base < total; base += (int64_t)gridDim.x * kWave) {
+  const int f0 = WF == 1 ? 0 : min(wave * per_wave, FR);
+  const int f1 = WF == 1 ? FR : min(f0 + per_wave, FR);
+  constexpr int STEP = 4 / WF * kWave;                    // outputs (of NO rows) a workgroup
+  for (int64_t base = (int64_t)blockIdx.x * STEP + (WF == 1 ? kWave * wave : 0); base < total;
+       base += (int64_t)gridDim.x * STEP) {
     const int64_t idx = min(base + lane, total - 1);      // clamped lanes never store
     const int r = (int)(idx / per_req);
     const int o0 = NO * (int)((idx % per_req) / E4), e = 4 * (int)(idx % E4);
@@ -369,20 +374,27 @@ __global__ __launch_bounds__(256) void lcb_request_bf16x4(
           }
         }
     }
-#pragma unroll
-    for (int j = 0; j < NO; ++j) part[wave][j][lane] = acc[j];
-    __syncthreads();
-    const int o = o0 + wave;                              // wave j finishes output row j
-    if (wave < NO && base + lane < total && o < O) {
-      const f32x4 s = ((part[0][wave][lane] + part[1][wave][lane]) + part[2][wave][lane]) + part[3][wave][lane];
+    auto store = [&](int o, f32x4 s) __attribute__((always_inline)) {
+      if (base + lane >= total || o >= O) return;
       if (o < OR) {
         *reinterpret_cast<u32x2*>(yr + ((int64_t)r * OR + o) * E + e) =
             u32x2{pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3])};
       } else {
         *reinterpret_cast<f32x4*>(z + ((int64_t)r * OC + (o - OR)) * E + e) = s;
       }
+    };
+    if constexpr (WF == 1) {
+#pragma unroll
+      for (int j = 0; j < NO; ++j) store(o0 + j, acc[j]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < NO; ++j) part[wave][j][lane] = acc[j];
+      __syncthreads();
+      if (wave < NO)                        // wave j finishes output row j
+        store(o0 + wave, ((part[0][wave][lane] + part[1][wave][lane]) + part[2][wave][lane]) +
+                             part[3][wave][lane]);
+      __syncthreads();                      // part is free for the next round
     }
-    __syncthreads();                        // part is free for the next round
   }
 }
 
@@ -401,14 +413,19 @@ hipError_t launch_typed(const LcbArgs& a, bool fast, hipStream_t s) {
     // 4 and 12 requests x 96 rows x 64 are faster with one (9.5 / 10.5, 13.6 / 14.3 us).
     const bool four = a.R * rows * (a.emb / 4) >= (int64_t)2 * cus * kWave;
     const int64_t per_req = (four ? (rows + 3) / 4 : rows) * (a.emb / 4);
-    const int64_t req_waves = (a.R * per_req + kWave - 1) / kWave;
+    // Up to 16 fields are one round of loads for a wave: nothing to split.
+    const bool whole = a.f_req <= 16;
+    const int outs = whole ? 4 * kWave : kWave;             // outputs a workgroup
+    const int64_t req_waves = (a.R * per_req + outs - 1) / outs;
     const int64_t blocks = req_waves < (1 << 22) ? req_waves : (1 << 22);   // they loop
-    e = launch_kernel(four && vecw ? lcb_request_bf16x4<4, true>
-                      : four ? lcb_request_bf16x4<4, false>
-                      : vecw ? lcb_request_bf16x4<1, true>
-                             : lcb_request_bf16x4<1, false>,
-                      dim3((uint32_t)blocks), dim3(256),
-                      s, static_cast<const bf16_t*>(a.x_req), static_cast<const bf16_t*>(a.w_rr),
+    auto pick = [&](auto wf) {
+      constexpr int WF = decltype(wf)::value;
+      return four ? (vecw ? lcb_request_bf16x4<4, true, WF> : lcb_request_bf16x4<4, false, WF>)
+                  : (vecw ? lcb_request_bf16x4<1, true, WF> : lcb_request_bf16x4<1, false, WF>);
+    };
+    e = launch_kernel(whole ? pick(std::integral_constant<int, 1>())
+                            : pick(std::integral_constant<int, 4>()),
+                      dim3((uint32_t)blocks), dim3(256), s, static_cast<const bf16_t*>(a.x_req), static_cast<const bf16_t*>(a.w_rr),
                       static_cast<const bf16_t*>(a.w_cr), static_cast<bf16_t*>(a.y_req), a.z,
                       (int)a.R, a.f_req, a.o_req, a.o_cand, a.emb);
   } else {

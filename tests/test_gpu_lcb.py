@@ -138,7 +138,8 @@ def test_lcb_deterministic_and_request_only(gpu_lib):
 @pytest.mark.parametrize("reqs", [5, 90], ids=["few", "many"])
 @pytest.mark.parametrize("f_req,o_req,emb,shift", [
     (1, 0, 64, 0), (3, 1, 128, 0), (4, 5, 64, 0), (6, 2, 128, 0), (16, 3, 64, 0), (20, 0, 128, 0),
-    (33, 7, 64, 0), (128, 64, 128, 0), (132, 6, 64, 0), (32, 5, 128, 1)])
+    (33, 7, 64, 0), (128, 64, 128, 0), (132, 6, 64, 0), (32, 5, 128, 1), (13, 5, 128, 1),
+    (17, 3, 64, 0)])
 def test_lcb_request_edges(gpu_lib, f_req, o_req, emb, shift, reqs):
     # Request side of the fast path: fields and output rows on and off the
     # fours that a load and a thread take, waves without fields, and weight
