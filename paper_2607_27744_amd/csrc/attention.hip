@@ -1194,7 +1194,7 @@ __global__ __launch_bounds__(1024) void group_scan(int32_t* __restrict__ hist, i
 // WHOLE (one block, N up to kGroupWholeCands): the counts are scanned here
 // too and the grouped offsets written, in one launch instead of three.
 constexpr int kGroupCounters = 32768;              // per-wave request counters in LDS (128 KiB)
-constexpr int64_t kGroupWholeCands = 32768;
+constexpr int64_t kGroupWholeCands = 8192;
 constexpr int kGroupAhead = 8;                     // rounds of 64 ids in flight
 
 template <bool WHOLE>
@@ -1507,8 +1507,11 @@ hipError_t launch_fast_mapped(const AttentionArgs& a, hipStream_t s) {
   while ((int64_t(1) << key_bits) < a.R) ++key_bits;
   const int32_t* base = hist;
   hipError_t e;
-  // One launch while a wave's walk (N / 16 candidates) stays within a few
-  // microseconds and every request has its counters in all 16 waves.
+  // One launch while its waves' walks (N / 16 candidates each) take no longer
+  // than the two launches it saves, and every request has its counters in all
+  // 16 waves. Whole call (us, one launch / three), 16 requests: 4,096: 13.7 /
+  // 17.7; 8,192: 18.9 / 21.1; 10,000: 19.1 / 18.2; 16,384: 23.2 / 19.5; 32,768:
+  // 36.5 / 22.0; 512 requests, 8,192: 21.8 / 25.2, 10,000: 28.1 / 25.6.
   if (a.N <= kGroupWholeCands && waves == 16) {
     e = launch_kernel(group_scatter<true>, dim3(1), dim3(1024), s, a.ids, a.N, (int)a.R, a.N, 1,
                       key_bits, base, grp_off, order);

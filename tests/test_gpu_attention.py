@@ -408,11 +408,12 @@ def test_attention_proj_with_plan(gpu_lib):
     assert_close(host(out), want, "proj planned")
 
 
-# The grouping's edges: one workgroup up to 32768 candidates with counters in
+# The grouping's edges: one workgroup up to 8192 candidates with counters in
 # all 16 waves (R <= 2048), then blocks with 16, 8 and 2 waves; the last
 # partial 64 of a wave's share; ids outside [0, R) clamped.
 @pytest.mark.parametrize("n,r", [(1, 1), (65, 2), (1025, 1), (3000, 2048), (3000, 2049),
-                                 (32768, 41), (32769, 41), (20000, 16384)])
+                                 (8192, 41), (8192, 2048), (8193, 41), (32768, 41),
+                                 (32769, 41), (20000, 16384)])
 def test_mapped_grouping_edges(gpu_lib, n, r):
     rng = np.random.default_rng(n + r)
     m = rng.integers(0, r, n).astype(np.int32)
