@@ -201,8 +201,8 @@ def ikbo_linear_combined(x_req, x_cand, w_cr, w_cc, cand_offsets, *, w_rr=None, 
         d_req = w_rr.shape[0]
         _need(w_rr.dtype == x_req.dtype and w_rr.is_contiguous(), "w_rr must match x_req")
         if b_req is not None:
-            _need(b_req.dtype == torch.float32 and b_req.shape == (d_req,),
-                  "b_req must be float32 [d_req]")
+            _need(b_req.dtype == torch.float32 and b_req.shape == (d_req,) and
+                  b_req.is_contiguous(), "b_req must be contiguous float32 [d_req]")
         if y_req is None:
             y_req = _new((n_req, d_req), x_req.dtype, x_req.device, stream)
         _need(y_req.shape == (n_req, d_req) and y_req.dtype == x_req.dtype and
@@ -231,7 +231,8 @@ def glm_linear(x_req, x_cand, w_rr, w_cr, w_cc, cand_offsets, *, b_req=None, b_c
     d_req = w_rr.shape[0]
     _need(w_rr.dtype == x_req.dtype and w_rr.is_contiguous(), "w_rr must match x_req")
     if b_req is not None:
-        _need(b_req.dtype == torch.float32 and b_req.shape == (d_req,), "b_req must be float32 [d_req]")
+        _need(b_req.dtype == torch.float32 and b_req.shape == (d_req,) and b_req.is_contiguous(),
+              "b_req must be contiguous float32 [d_req]")
     if y_req is None:
         y_req = _new((n_req, d_req), x_req.dtype, x_req.device, stream)
     _need(y_req.shape == (n_req, d_req) and y_req.dtype == x_req.dtype and y_req.is_contiguous(),
