@@ -121,32 +121,55 @@ def _spoiled(value, name=""):
         yield "text"
 
 
+class _Spy:
+    """The native module, noting whether the last call was taken there."""
+
+    def __init__(self, module):
+        self.module, self.taken = module, None
+
+    def __getattr__(self, name):
+        def call(*args):
+            done = getattr(self.module, name)(*args)
+            self.taken = done is not None
+            return done
+        return call
+
+
+# Valid calls that the native path leaves to ops.py: weights or offsets of a
+# request term that is not there.
+LEFT = {("linear", "x_req"), ("linear add", "x_req"), ("mapped", "x_req"), ("mlp2", "x_req")}
+
+
 @pytest.mark.parametrize("name", sorted(_calls() if torch.cuda.is_available() else ["none"]))
 def test_same_as_the_python_path(gpu_lib, name, monkeypatch):
     torch.manual_seed(0)
     fn, kw = _calls()[name]
-    native = ops._native()
-    cases = [kw]
+    native = _Spy(ops._native())
+    cases = [("", kw)]
     for key, value in kw.items():
-        cases += [dict(kw, **{key: v}) for v in _spoiled(value, key)]
+        cases += [(key, dict(kw, **{key: v})) for v in _spoiled(value, key)]
     if name != "plan":
         first = fn(**kw)
         outs = first if isinstance(first, tuple) else (first,)
         key = {"glm": "y_cand", "lcb": "y_cand", "lcb mapped": "y_cand"}.get(name, "out")
         given = outs[1] if key == "y_cand" else outs[0]
-        cases += [dict(kw, **{key: v}) for v in [torch.empty_like(given), *_spoiled(given)]]
-        if "request" not in name:
-            cases.append(dict(kw, stream=torch.cuda.current_stream()))
-    taken = 0
-    for case in cases:
+        cases += [(key, dict(kw, **{key: v})) for v in [torch.empty_like(given), *_spoiled(given)]]
+    cases.append(("stream", dict(kw, stream=torch.cuda.current_stream())))
+    valid = 0
+    for key, case in cases:
         monkeypatch.setattr(ops, "_binding", native)
+        native.taken = None
         a = _outcome(fn, case)
         monkeypatch.setattr(ops, "_binding", PYTHON)
         b = _outcome(fn, case)
         assert _same(a, b), (name, {k: (tuple(v.shape), v.dtype, str(v.device)) if torch.is_tensor(v)
                                     else v for k, v in case.items()}, a, b)
-        taken += not isinstance(a, tuple)
-    assert taken > 1
+        if isinstance(a, tuple):                # an error, the same on both paths
+            assert key and not native.taken
+            continue
+        valid += 1
+        assert bool(native.taken) != ((name, key) in LEFT and case[key] is None), (name, key)
+    assert valid > 2
     monkeypatch.setattr(ops, "_binding", native)
     if "out" in kw or name in ("linear", "attention"):
         out = torch.empty_like(fn(**kw))
