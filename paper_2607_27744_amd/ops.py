@@ -565,7 +565,8 @@ def dca_request_attention(q_req, k, v, kv_offsets, *, scale=None, out=None, stre
                       scale, out, stream)
 
 
-_IDENTITY = {}
+_IDENTITY = {}       # (power of two, device): [0, 1, ..]
+_IDENTITY_VIEWS = {}  # (R, device): its first R + 1 entries; a slice costs 1 us
 
 
 def _identity_offsets(n_req, device, stream):
@@ -573,18 +574,23 @@ def _identity_offsets(n_req, device, stream):
     (power of two, device), complete before any stream reads it. Under capture
     an array that is not there yet becomes part of the graph instead, which
     fills it on every replay."""
-    size = 1 << max(n_req + 1, 1024).bit_length()
-    key = (size, str(device))
+    view = _IDENTITY_VIEWS.get((n_req, device))
+    if view is not None:
+        return view
+    key = (1 << max(n_req + 1, 1024).bit_length(), device)
     if key not in _IDENTITY:
         if device.type == "cuda" and torch.cuda.is_current_stream_capturing():
             t = _new(n_req + 1, torch.int32, device, stream, scratch=True)
             with torch.cuda.stream(stream):
                 return torch.arange(n_req + 1, dtype=torch.int32, device=device, out=t)
-        t = torch.arange(size, dtype=torch.int32, device=device)
+        t = torch.arange(key[0], dtype=torch.int32, device=device)
         if t.is_cuda:
             torch.cuda.current_stream(device).synchronize()
         _IDENTITY[key] = t
-    return _IDENTITY[key][:n_req + 1]
+    if len(_IDENTITY_VIEWS) >= 1024:
+        _IDENTITY_VIEWS.clear()
+    view = _IDENTITY_VIEWS[n_req, device] = _IDENTITY[key][:n_req + 1]
+    return view
 
 
 def _attention(q, k, v, cand_offsets, cand_ids, kv_offsets, scale, out, stream, workspace=None,

@@ -69,6 +69,7 @@ def test_identity_offsets_first_needed_under_capture(gpu_lib, monkeypatch):
     # Request-side attention builds its offsets on first use. A graph's own
     # memory, unwritten before its first replay, must not serve eager calls.
     monkeypatch.setattr(ops, "_IDENTITY", {})
+    monkeypatch.setattr(ops, "_IDENTITY_VIEWS", {})
     kw = _calls()["attention request"][1]
     n = kw["q_req"].shape[0]
     offsets = dict(cand_offsets=torch.arange(n + 1, dtype=torch.int32, device="cuda"))
@@ -78,7 +79,7 @@ def test_identity_offsets_first_needed_under_capture(gpu_lib, monkeypatch):
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         ops.dca_request_attention(**kw, out=out)
-    assert not ops._IDENTITY
+    assert not ops._IDENTITY and not ops._IDENTITY_VIEWS
     for _ in range(3):
         assert torch.equal(ops.dca_request_attention(**kw), want)
         out.zero_()
