@@ -106,9 +106,8 @@ const char* rocs_last_error_message(void);
  * The request-side GEMM is a launch of its own; rocs_ikbo_linear_combined
  * runs it inside the candidate kernel instead (Section 4.2.3).
  *
- * Limits: every size below 2^31. Off the fast path the general kernels run
- * one thread per output element, so N * d_out must stay below 2^32
- * (ROCS_ERR_UNSUPPORTED otherwise).
+ * Limits: every size below 2^31. Off the fast path N * d_out must stay below
+ * 2^32 (ROCS_ERR_UNSUPPORTED otherwise).
  * ---------------------------------------------------------------------------
  */
 size_t rocs_ikbo_linear_workspace_size(int64_t num_requests, int64_t num_cand,
@@ -281,9 +280,8 @@ int32_t rocs_ikbo_linear_mapped(const void* x_req, int64_t k_req,
  * general kernel.
  *
  * Limits: N * q_len below 2^31 and num_heads below 2^16. The general kernel
- * runs one wave per query row and head, so it takes N * q_len below 2^26;
- * the fast path takes (R + N * q_len / 128) * num_heads below 2^24. Larger
- * calls return ROCS_ERR_UNSUPPORTED.
+ * takes N * q_len below 2^26, the fast path (R + N * q_len / 128) * num_heads
+ * below 2^24. Larger calls return ROCS_ERR_UNSUPPORTED.
  * ---------------------------------------------------------------------------
  */
 int32_t rocs_dca_attention(const void* q, const void* k, const void* v,

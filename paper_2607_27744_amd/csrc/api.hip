@@ -207,11 +207,11 @@ int32_t linear_impl(const char* name, bool mapped, const void* x_req, int64_t k_
                     aligned(out, 16) &&
                     (!full || (rs.d_req % 4 == 0 && aligned(rs.w_rr, 16) &&
                                aligned(rs.b_rr, 16) && aligned(rs.y_req, 8)));
-  // The general kernels run one thread per output element (and the request
-  // kernel one per request-side element); keep their grids under 2^32 items.
+  // The general path takes fewer than 2^32 values of each output. (Its launches
+  // would not need that: they loop over tiles. It is the interface's limit.)
   if (!fast && ((N * d_out) >> 32 != 0 || (R * (d_out + (full ? rs.d_req : 0))) >> 32 != 0 ||
                 (full && (R * rs.d_req) >> 32 != 0)))
-    return fail(ROCS_ERR_UNSUPPORTED, "%s: the general kernel's grid would exceed 2^32 threads "
+    return fail(ROCS_ERR_UNSUPPORTED, "%s: the general path takes fewer than 2^32 output values "
                 "(N * d_out = %lld); the bf16 fast path has no such limit", name,
                 (long long)(N * d_out));
   const hipError_t e = rocs::launch_linear(a, fast, static_cast<hipStream_t>(stream));
@@ -427,10 +427,10 @@ int32_t attention_impl(const char* name, bool mapped, const void* q, const void*
                     stride < (int64_t(1) << 24) &&
                     aligned(q, 16) && aligned(k, 16) && aligned(v, 16) && aligned(out, 16) &&
                     aligned(residual, 16) && aligned(out_sum, 16) && aligned(proj_w, 16);
-  // Launch limits: a grid may hold fewer than 2^32 work items. The general
-  // kernel runs one 64-lane wave per (query row, head) with the rows on the
-  // grid's x axis; the tiled kernel runs 256 lanes per (head, tile slot),
-  // R + ceil(N q_len / 128) slots per head.
+  // Launch limits: a grid may hold fewer than 2^32 work items. The tiled kernel
+  // runs 256 lanes per (head, tile slot), R + ceil(N q_len / 128) slots per
+  // head. The general kernel's rows stand on the grid's x axis, 256 lanes for
+  // up to 16 of them: its limit of 2^26 rows is the interface's.
   // The mapped form runs the tiled kernel on the candidates grouped by
   // request when the grouping fits (R and the per-block count table), with
   // the grouping in the caller's workspace; otherwise the general kernel.
@@ -449,8 +449,8 @@ int32_t attention_impl(const char* name, bool mapped, const void* q, const void*
       return fail(ROCS_ERR_INVALID_ARGUMENT, "%s: workspace overlaps an argument", name);
   }
   if (!tiled && (N * q_len) >= (int64_t(1) << 26))
-    return fail(ROCS_ERR_UNSUPPORTED, "%s: N * q_len = %lld query rows exceed the general "
-                "kernel's grid (2^26 rows)", name, (long long)(N * q_len));
+    return fail(ROCS_ERR_UNSUPPORTED, "%s: N * q_len = %lld query rows; the general kernel takes "
+                "fewer than 2^26", name, (long long)(N * q_len));
   if (tiled && (R + (N * q_len + 127) / 128) * num_heads >= (int64_t(1) << 24))
     return fail(ROCS_ERR_UNSUPPORTED, "%s: (R + N * q_len / 128) * num_heads tiles exceed the "
                 "grid limit (2^24)", name);

@@ -10,8 +10,9 @@
 //   2. candidate side: a bf16 MFMA GEMM over the candidate batch whose
 //      accumulators start from Z[m_n] + b, so the request term is added in
 //      registers and only the final activations are written.
-// The general (fp32 / unaligned) path keeps the same two-step structure with
-// plain FMA kernels.
+// The general path (fp32, sizes or pointers off the fast path's alignment) runs
+// on the fp32 matrix instructions: two steps for large calls, for small ones a
+// single launch that takes the request term into the candidates' product.
 #include "common.h"
 #include "kernels.h"
 #include "launch.h"

@@ -371,8 +371,8 @@ def test_combined_entry_point_argument_errors(lib):
 
 @no_gpu
 def test_grid_limits_are_unsupported(lib):
-    # The general kernels run one thread (or wave) per output element or
-    # query row; grids of 2^32 work items or more are refused up front.
+    # Off the fast path: 2^32 output values of a linear and 2^26 query rows of
+    # an attention are refused up front, as is a grid of 2^32 work items.
     n = 1 << 30
     st = lib.rocs_ikbo_linear(None, 0, FAR[0], None, 8, None, FAR[1], None, None, 0, n, 8,
                               0, 0, FAR[2], None, 0, None)      # fp32: general kernel
