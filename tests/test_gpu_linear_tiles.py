@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 
 # counts, k_req, k_cand, d_out: below / above 256 tiles of 128 x 128 (the tile
 # switch on 256 CUs), N and D at and off tile edges, K of one slab, off the
-# 32- and 64-wide slabs, and the shortest.
+# 32- and 64-wide slabs, the shortest, and both sides of 256 (the waves' places
+# with a residual).
 CASES = [
     ([1], 8, 8, 4),
     ([63, 1, 0, 64], 16, 64, 64),
@@ -24,6 +25,7 @@ CASES = [
     ([300, 0, 5], 40, 200, 132),
     ([5000, 11, 3181, 0], 64, 104, 516),
     ([2047, 6100, 45], 72, 320, 520),
+    ([4001, 0, 4100], 16, 264, 644),
 ]
 
 
